@@ -72,8 +72,9 @@ int launch_pack_links(const Geom& g, const double* aos, void* out, int prec, int
                       double scale, hipStream_t s);
 int launch_pack_field(const Geom& g, const double* aos, int ncol, int nc, FieldRef out, int prec, int par_sel,
                       hipStream_t s);
+// zero: with par_sel 0 or 1, the sites of the other parity are written as zeros
 int launch_unpack_field(const Geom& g, FieldRef in, int prec, int ncol, int nc, double* aos, int par_sel,
-                        hipStream_t s);
+                        hipStream_t s, bool zero = false);
 int launch_convert(FieldRef dst, int pdst, FieldRef src, int psrc, int nc, int ncol, int npar, int Vh,
                    hipStream_t s);
 double link_maxabs(const double* aos, int64_t n, hipStream_t s);

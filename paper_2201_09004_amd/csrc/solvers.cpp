@@ -1564,7 +1564,6 @@ int solve(lq_ctx* c, const lq_action* act, lq_field* f, const lq_params* prm, in
     }
     // output
     const size_t colsz = (size_t)2 * g.Vh * 3 * 2;  // doubles per column
-    if (launch_fill_zero(x_dev, sizeof(double) * colsz * ncol, s)) return fail(LQ_EDEVICE, "zero");
     Vec yo;
     if (prm->reconstruct_full) {
       Vec yf = make_vec(g, 64, 3, ncol, 2, 0, s);
@@ -1584,7 +1583,7 @@ int solve(lq_ctx* c, const lq_action* act, lq_field* f, const lq_params* prm, in
         if (launch_unpack_field(g, v.f, 64, n_rhs, 3, dst, 2, s)) return fail(LQ_EDEVICE, "unpack");
       } else {
         Vec v = view(y, k * n_rhs, n_rhs);
-        if (launch_unpack_field(g, v.f, 64, n_rhs, 3, dst, 0, s)) return fail(LQ_EDEVICE, "unpack");
+        if (launch_unpack_field(g, v.f, 64, n_rhs, 3, dst, 0, s, true)) return fail(LQ_EDEVICE, "unpack");
       }
     }
   } else {
@@ -1616,26 +1615,31 @@ int apply_op(lq_ctx* c, const lq_action* act, lq_field* f, int op, int prec, int
   const int kind = act->kind;
   const int nc = kind == LQ_HISQ ? 3 : 12;
   if ((kind == LQ_HISQ) != (f->type == 1)) return fail(LQ_EINVAL, "field type does not match the action");
+  int e = 0;
+  // the even-site operators move the even sites alone: one pack, and one unpack
+  // that writes the odd sites' zeros with them
+  const bool even = kind == LQ_HISQ ? op == LQ_OP_NORMAL_EVEN : op == LQ_OP_SCHUR;
+  if (even) {
+    if (kind != LQ_HISQ && kind != LQ_TM_CLOVER) return fail(LQ_EINVAL, "Schur operator needs the twisted-clover action");
+    Vec ie = make_vec(g, prec, nc, n_rhs, 1, 0, s), oe = make_vec(g, prec, nc, n_rhs, 1, 0, s),
+        to = make_vec(g, prec, nc, n_rhs, 1, 1, s);
+    if (!ie.ok() || !oe.ok() || !to.ok()) return fail(LQ_ENOMEM, "apply buffers");
+    if (launch_pack_field(g, in_dev, n_rhs, nc, ie.f, prec, 0, s)) return fail(LQ_EDEVICE, "pack");
+    e = kind == LQ_HISQ ? stag_normal_even(env, prec, oe, ie, to, nullptr, act->m * act->m)
+                        : tm_schur(env, prec, oe, ie, to);
+    if (e) return e;
+    if (launch_unpack_field(g, oe.f, prec, n_rhs, nc, out_dev, 0, s, true)) return fail(LQ_EDEVICE, "unpack");
+    return hipStreamSynchronize(s) == hipSuccess ? 0 : fail(LQ_EDEVICE, "sync");
+  }
   Vec in = make_vec(g, prec, nc, n_rhs, 2, 0, s);
   Vec out = make_vec(g, prec, nc, n_rhs, 2, 0, s);
   if (!in.ok() || !out.ok()) return fail(LQ_ENOMEM, "apply buffers");
   if (launch_pack_field(g, in_dev, n_rhs, nc, in.f, prec, 2, s)) return fail(LQ_EDEVICE, "pack");
-  int e = 0;
-  int par_sel = 2;
   if (kind == LQ_HISQ) {
     if (op == LQ_OP_D) e = stag_D(env, prec, out, in, false);
     else if (op == LQ_OP_DDAG) e = stag_D(env, prec, out, in, true);
     else if (op == LQ_OP_HOP) e = stag_hop(env, prec, out, in);
-    else if (op == LQ_OP_NORMAL_EVEN) {
-      Vec ie = make_vec(g, prec, 3, n_rhs, 1, 0, s), oe = make_vec(g, prec, 3, n_rhs, 1, 0, s),
-          to = make_vec(g, prec, 3, n_rhs, 1, 1, s);
-      if (!ie.ok() || !oe.ok() || !to.ok()) return fail(LQ_ENOMEM, "apply buffers");
-      if (launch_pack_field(g, in_dev, n_rhs, 3, ie.f, prec, 0, s)) return fail(LQ_EDEVICE, "pack");
-      if ((e = stag_normal_even(env, prec, oe, ie, to, nullptr, act->m * act->m))) return e;
-      if (launch_fill_zero(out_dev, sizeof(double) * 2 * 3 * 2 * (size_t)g.Vh * n_rhs, s)) return fail(LQ_EDEVICE, "zero");
-      if (launch_unpack_field(g, oe.f, prec, n_rhs, 3, out_dev, 0, s)) return fail(LQ_EDEVICE, "unpack");
-      return hipStreamSynchronize(s) == hipSuccess ? 0 : fail(LQ_EDEVICE, "sync");
-    } else return fail(LQ_EINVAL, "op not defined for HISQ");
+    else return fail(LQ_EINVAL, "op not defined for HISQ");
   } else {
     if (kind == LQ_OVERLAP && prec == 64 && op != LQ_OP_HW && op != LQ_OP_HOP) {
       if ((e = overlap_prepare(env))) return e;
@@ -1656,18 +1660,6 @@ int apply_op(lq_ctx* c, const lq_action* act, lq_field* f, int op, int prec, int
         if (kind != LQ_TM_CLOVER) return fail(LQ_EINVAL, "site term needs the twisted-clover action");
         e = tm_site(env, prec, out, in, op == LQ_OP_SITE_INV);
         break;
-      case LQ_OP_SCHUR: {
-        if (kind != LQ_TM_CLOVER) return fail(LQ_EINVAL, "Schur operator needs the twisted-clover action");
-        Vec ie = make_vec(g, prec, 12, n_rhs, 1, 0, s), oe = make_vec(g, prec, 12, n_rhs, 1, 0, s),
-            to = make_vec(g, prec, 12, n_rhs, 1, 1, s);
-        if (!ie.ok() || !oe.ok() || !to.ok()) return fail(LQ_ENOMEM, "apply buffers");
-        if (launch_pack_field(g, in_dev, n_rhs, 12, ie.f, prec, 0, s)) return fail(LQ_EDEVICE, "pack");
-        if ((e = tm_schur(env, prec, oe, ie, to))) return e;
-        if (launch_fill_zero(out_dev, sizeof(double) * 2 * 12 * 2 * (size_t)g.Vh * n_rhs, s))
-          return fail(LQ_EDEVICE, "zero");
-        if (launch_unpack_field(g, oe.f, prec, n_rhs, 12, out_dev, 0, s)) return fail(LQ_EDEVICE, "unpack");
-        return hipStreamSynchronize(s) == hipSuccess ? 0 : fail(LQ_EDEVICE, "sync");
-      }
       case LQ_OP_HW: e = hw_apply(env, prec, out, in); break;
       case LQ_OP_SIGN:
         if (kind != LQ_OVERLAP) return fail(LQ_EINVAL, "sign function needs the overlap action");
@@ -1678,7 +1670,7 @@ int apply_op(lq_ctx* c, const lq_action* act, lq_field* f, int op, int prec, int
     }
   }
   if (e) return e;
-  if (launch_unpack_field(g, out.f, prec, n_rhs, nc, out_dev, par_sel, s)) return fail(LQ_EDEVICE, "unpack");
+  if (launch_unpack_field(g, out.f, prec, n_rhs, nc, out_dev, 2, s)) return fail(LQ_EDEVICE, "unpack");
   return hipStreamSynchronize(s) == hipSuccess ? 0 : fail(LQ_EDEVICE, "sync");
 }
 
