@@ -114,11 +114,7 @@ lq_status lq_init(int device, lq_ctx** ctx) {
     delete c;
     return (lq_status)fail(LQ_EDEVICE, "stream creation failed");
   }
-  hipMemPool_t pool;
-  if (hipDeviceGetDefaultMemPool(&pool, device) == hipSuccess) {
-    uint64_t thr = UINT64_MAX;
-    hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &thr);
-  }
+  work_context(device, 1);
   (void)hipGetLastError();
   *ctx = c;
   return LQ_OK;
@@ -132,7 +128,9 @@ lq_status lq_finalize(lq_ctx* c) {
   eig_release(c);
   for (auto e : c->event_pool) hipEventDestroy(e);
   if (c->partial) hipFree(c->partial);
+  work_stream_gone(c->device, c->stream);
   hipStreamDestroy(c->stream);
+  work_context(c->device, -1);
   delete c;
   return LQ_OK;
 }
@@ -150,8 +148,9 @@ static lq_status load_common(lq_ctx* c, const lq_geom* geom, const double* a, co
   const size_t bytes = (size_t)2 * f->g.Vh * 4 * 18 * sizeof(double);
   hipStream_t s = dev ? (hipStream_t)stream : c->stream;
   const hipMemcpyKind kind = dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-  if (hipMalloc(&f->aos, bytes) != hipSuccess || (type == 1 && hipMalloc(&f->aos2, bytes) != hipSuccess)) {
-    (void)hipGetLastError();
+  f->aos = (double*)device_malloc(bytes);
+  if (f->aos && type == 1) f->aos2 = (double*)device_malloc(bytes);
+  if (!f->aos || (type == 1 && !f->aos2)) {
     if (f->aos) hipFree(f->aos);
     delete f;
     return (lq_status)fail(LQ_ENOMEM, "gauge field allocation");
@@ -224,7 +223,9 @@ lq_status lq_apply_dev(lq_ctx* c, const lq_action* act, const lq_field* g, int o
   if (e) return (lq_status)e;
   if (n_rhs == 0) return LQ_OK;
   hipSetDevice(c->device);
-  return (lq_status)apply_op(c, act, const_cast<lq_field*>(g), op, prec, n_rhs, in, out, (hipStream_t)stream);
+  e = apply_op(c, act, const_cast<lq_field*>(g), op, prec, n_rhs, in, out, (hipStream_t)stream);
+  if (e) (void)hipStreamSynchronize((hipStream_t)stream);  // its blocks wait for this stream, which the caller may destroy
+  return (lq_status)e;
 }
 
 lq_status lq_apply_noalloc(lq_ctx* c, const lq_action* act, const lq_field* g, int op, int prec, int n_rhs,
@@ -297,6 +298,7 @@ lq_status lq_solve_dev(lq_ctx* c, const lq_action* act, const lq_field* g, const
   if (n_rhs == 0) return LQ_OK;
   hipSetDevice(c->device);
   e = solve(c, act, const_cast<lq_field*>(g), prm, n_rhs, b, x, st, (hipStream_t)stream);
+  if (e) (void)hipStreamSynchronize((hipStream_t)stream);  // as in lq_apply_dev
   if (st) st->status = e;
   return (lq_status)e;
 }
@@ -378,9 +380,8 @@ lq_status lq_copy_bandwidth(lq_ctx* c, size_t bytes, int reps, double* gbs) {
   if (!c || !gbs || bytes < 16 || reps < 1) return (lq_status)fail(LQ_EINVAL, "need ctx, gbs, bytes >= 16, reps >= 1");
   hipSetDevice(c->device);
   bytes = bytes / 16 * 16;
-  void *a = nullptr, *b = nullptr;
-  if (hipMalloc(&a, bytes) != hipSuccess || hipMalloc(&b, bytes) != hipSuccess) {
-    (void)hipGetLastError();
+  void *a = device_malloc(bytes), *b = a ? device_malloc(bytes) : nullptr;
+  if (!b) {
     if (a) hipFree(a);
     return (lq_status)fail(LQ_ENOMEM, "copy buffers");
   }

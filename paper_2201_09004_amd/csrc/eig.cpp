@@ -553,7 +553,7 @@ int eigs(lq_ctx* c, const lq_action* act, lq_field* f, int which, int nev, doubl
       es.vals = mu;
       es.res = res;
       const size_t bytes = vec_bytes(g, 64, 12, nev, 2);
-      if (hipMalloc(&es.vecs, bytes) != hipSuccess) return fail(LQ_ENOMEM, "eigenvector storage");
+      if (!(es.vecs = device_malloc(bytes))) return fail(LQ_ENOMEM, "eigenvector storage");
       if (hipMemcpyAsync(es.vecs, V.f.data, bytes, hipMemcpyDeviceToDevice, s) != hipSuccess)
         return fail(LQ_EDEVICE, "copy");
       es.n = nev;
@@ -568,7 +568,7 @@ int eigs(lq_ctx* c, const lq_action* act, lq_field* f, int which, int nev, doubl
   }
   if (which == LQ_EIG_HW) {
     const size_t bytes = vec_bytes(g, 64, 12, nev, 2);
-    if (hipMalloc(&sets[0].vecs, bytes) != hipSuccess) return fail(LQ_ENOMEM, "eigenvector storage");
+    if (!(sets[0].vecs = device_malloc(bytes))) return fail(LQ_ENOMEM, "eigenvector storage");
     if (hipMemcpyAsync(sets[0].vecs, V.f.data, bytes, hipMemcpyDeviceToDevice, s) != hipSuccess)
       return fail(LQ_EDEVICE, "copy");
     sets[0].n = nev;

@@ -142,6 +142,21 @@ struct Prof {
 };
 void prof_flush(lq_ctx* c);
 
+// ------------------------------------------------------------------ working memory (pool.cpp)
+// Device blocks in the order of stream s: given back, a block serves later
+// requests on s.  nullptr when the device has no room.
+void* work_alloc(size_t bytes, hipStream_t s);
+void work_free(void* p, hipStream_t s);
+// a library stream is gone, its work done: its blocks may serve any stream
+void work_stream_gone(int device, hipStream_t s);
+// contexts of a device (+1, -1): the last one gives every waiting block back
+void work_context(int device, int change);
+// hipMalloc for what lives with a field; waiting blocks make room when it fails
+void* device_malloc(size_t bytes);
+// pinned host blocks; *got is the size to give back
+double* pinned_alloc(size_t bytes, size_t* got);
+void pinned_free(double* p, size_t got);
+
 // ------------------------------------------------------------------ vectors
 // A set of ncol columns of one field type (nc = 12 Wilson, 3 staggered) and
 // precision, storing npar parities per column (npar = 1: parity `par0` only).
@@ -182,7 +197,7 @@ struct DBuf {
   DBuf(DBuf&& o) noexcept : p(o.p), n(o.n), s(o.s) { o.p = nullptr; }
   DBuf& operator=(DBuf&& o) noexcept {
     if (this != &o) {
-      if (p) hipFreeAsync(p, s);
+      work_free(p, s);
       p = o.p;
       n = o.n;
       s = o.s;

@@ -24,24 +24,12 @@ namespace lq {
 namespace {
 
 int upload_ints(int** dst, const std::vector<int>& v, hipStream_t s) {
-  if (hipMalloc((void**)dst, v.size() * sizeof(int)) != hipSuccess) {
-    (void)hipGetLastError();
-    *dst = nullptr;
-    return fail(LQ_ENOMEM, "multigrid maps");
-  }
+  *dst = (int*)device_malloc(v.size() * sizeof(int));
+  if (!*dst) return fail(LQ_ENOMEM, "multigrid maps");
   if (hipMemcpyAsync(*dst, v.data(), v.size() * sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess)
     return fail(LQ_EDEVICE, "multigrid maps");
   return 0;
-}
-
-void* dev_alloc(size_t bytes) {
-  void* p = nullptr;
-  if (hipMalloc(&p, bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    return nullptr;
-  }
-  return p;
 }
 
 }  // namespace
@@ -132,10 +120,10 @@ int mg_build(OpEnv& e, MgHier& h, Vec& vecs) {
   const int n2 = 2 * h.nv;
   const size_t nq = (size_t)h.Vc * h.B * 2 * h.nv * 6;  // complex entries of Q
   const size_t nd = (size_t)h.Vc * 9 * n2 * n2;          // complex entries of Dc
-  h.Q64 = dev_alloc(nq * 16);
-  h.Q32 = dev_alloc(nq * 8);
-  h.Dc64 = dev_alloc(nd * 16);
-  h.Dc32 = dev_alloc(nd * 8);
+  h.Q64 = device_malloc(nq * 16);
+  h.Q32 = device_malloc(nq * 8);
+  h.Dc64 = device_malloc(nd * 16);
+  h.Dc32 = device_malloc(nd * 8);
   if (!h.Q64 || !h.Q32 || !h.Dc64 || !h.Dc32) return fail(LQ_ENOMEM, "multigrid basis and coarse operator");
   DBuf bad(sizeof(int), s);
   if (!bad.p) return fail(LQ_ENOMEM, "multigrid");
@@ -164,8 +152,8 @@ int mg_build(OpEnv& e, MgHier& h, Vec& vecs) {
     }
   if (launch_mg_narrow(h.Dc64, h.Dc32, (int64_t)nd, s)) return fail(LQ_EDEVICE, "multigrid coarse operator");
   // the even-odd preconditioned coarse operator: A^{-1} and A^{-1} Dc[d]
-  h.Ahat64 = dev_alloc(nd * 16);
-  h.Ahat32 = dev_alloc(nd * 8);
+  h.Ahat64 = device_malloc(nd * 16);
+  h.Ahat32 = device_malloc(nd * 8);
   DBuf work((size_t)h.Vc * n2 * 2 * n2 * 16, s);
   if (!h.Ahat64 || !h.Ahat32 || !work.p) return fail(LQ_ENOMEM, "multigrid coarse operator");
   if (launch_fill_zero(bad.p, sizeof(int), s) || launch_mg_site_inverse(m, h.Dc64, h.Ahat64, work.p, bad.as<int>(), s) ||

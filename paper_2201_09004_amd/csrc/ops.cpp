@@ -109,11 +109,8 @@ Vec make_vec(const Geom& g, int prec, int nc, int ncol, int npar, int par0, hipS
   v.f.npar = npar;
   v.f.Vh = g.Vh;
   if (ncol == 0) return v;
-  void* p = nullptr;
-  if (hipMallocAsync(&p, v.bytes, s) != hipSuccess) {
-    (void)hipGetLastError();
-    return v;
-  }
+  void* p = work_alloc(v.bytes, s);
+  if (!p) return v;
   v.f.data = p;
   v.f.norm = sep_norm(prec, nc) ? (float*)((char*)p + mainr) : nullptr;
   return v;
@@ -147,7 +144,7 @@ Vec vec_at(const Geom& g, int prec, int nc, int ncol, int npar, int par0, void* 
 
 Vec& Vec::operator=(Vec&& o) noexcept {
   if (this != &o) {
-    if (f.data && owner) hipFreeAsync(f.data, s);
+    if (f.data && owner) work_free(f.data, s);
     f = o.f;
     prec = o.prec;
     nc = o.nc;
@@ -163,7 +160,7 @@ Vec& Vec::operator=(Vec&& o) noexcept {
   return *this;
 }
 Vec::~Vec() {
-  if (f.data && owner) hipFreeAsync(f.data, s);
+  if (f.data && owner) work_free(f.data, s);
 }
 Vec view(const Vec& v, int c0, int n) {
   Vec r;
@@ -213,14 +210,9 @@ int vec_swap_cols(Vec& v, int a, int b) {
 }
 
 DBuf::DBuf(size_t bytes, hipStream_t st) : n(bytes), s(st) {
-  if (bytes && hipMallocAsync(&p, bytes, s) != hipSuccess) {
-    (void)hipGetLastError();
-    p = nullptr;
-  }
+  if (bytes) p = work_alloc(bytes, s);
 }
-DBuf::~DBuf() {
-  if (p) hipFreeAsync(p, s);
-}
+DBuf::~DBuf() { work_free(p, s); }
 
 // ------------------------------------------------------------------ fields
 int ensure_links(OpEnv& e, int prec) {
@@ -234,8 +226,8 @@ int ensure_links(OpEnv& e, int prec) {
     if (e.noalloc) return fail(LQ_EINVAL, "links of this precision are not resident (an earlier lq_apply or lq_solve "
                                           "at this precision packs them)");
     const int ne = rc ? 6 : 9;
-    void* p = nullptr;
-    if (hipMalloc(&p, esz * ne * 8 * (size_t)f->g.Vh) != hipSuccess) return fail(LQ_ENOMEM, "link allocation");
+    void* p = device_malloc(esz * ne * 8 * (size_t)f->g.Vh);
+    if (!p) return fail(LQ_ENOMEM, "link allocation");
     int r = launch_pack_links(f->g, f->aos, p, prec, ne, 0, 1.0, e.s);
     // complete before publishing: other streams (server engines, API calls) may use the field next
     if (r || hipStreamSynchronize(e.s) != hipSuccess) return fail(LQ_EDEVICE, "pack links");
@@ -253,10 +245,9 @@ int ensure_links(OpEnv& e, int prec) {
     if (!(sf > 0)) sf = 1.0;
     if (!(sl > 0)) sl = 1.0;
   }
-  void *pf = nullptr, *pl = nullptr;
   const size_t bytes = esz * 9 * 8 * (size_t)f->g.Vh;
-  if (hipMalloc(&pf, bytes) != hipSuccess || hipMalloc(&pl, bytes) != hipSuccess)
-    return fail(LQ_ENOMEM, "HISQ link allocation");
+  void *pf = device_malloc(bytes), *pl = device_malloc(bytes);
+  if (!pf || !pl) return fail(LQ_ENOMEM, "HISQ link allocation");
   if (launch_pack_links(f->g, f->aos, pf, prec, 9, 1, sf, e.s) ||
       launch_pack_links(f->g, f->aos2, pl, prec, 9, 3, sl, e.s) || hipStreamSynchronize(e.s) != hipSuccess)
     return fail(LQ_EDEVICE, "pack HISQ links");
@@ -284,14 +275,14 @@ int ensure_clover(OpEnv& e, int prec) {
   Clover& c = f->clover[key];
   const size_t nH = 2 * 2 * 18 * (size_t)f->g.Vh, nA = 2 * 2 * 36 * (size_t)f->g.Vh;  // T2 elements
   if (!c.H[0]) {
-    if (hipMalloc(&c.H[0], nH * 16) != hipSuccess || hipMalloc(&c.Ainv[0], nA * 16) != hipSuccess)
+    if (!(c.H[0] = device_malloc(nH * 16)) || !(c.Ainv[0] = device_malloc(nA * 16)))
       return fail(LQ_ENOMEM, "clover allocation");
     if (launch_clover_build(f->g, f->links[0][0], e.act.c_sw, e.act.m, e.act.mu, c.H[0], c.Ainv[0], e.s) ||
         hipStreamSynchronize(e.s) != hipSuccess)
       return fail(LQ_EDEVICE, "clover build");
   }
   if (prec == 32 && !c.H[1]) {
-    if (hipMalloc(&c.H[1], nH * 8) != hipSuccess || hipMalloc(&c.Ainv[1], nA * 8) != hipSuccess)
+    if (!(c.H[1] = device_malloc(nH * 8)) || !(c.Ainv[1] = device_malloc(nA * 8)))
       return fail(LQ_ENOMEM, "clover allocation");
     if (launch_clover_convert(c.H[0], c.H[1], (int64_t)nH, e.s) ||
         launch_clover_convert(c.Ainv[0], c.Ainv[1], (int64_t)nA, e.s) || hipStreamSynchronize(e.s) != hipSuccess)
@@ -388,7 +379,6 @@ static void apply_shape(Args& A, const Shape& sh) {
 template <typename Args, typename LaunchFn>
 static int tuned(lq_ctx* c, const std::string& key, Args& A, size_t out_bytes, int prec,
                  const std::vector<int>& nrs, hipStream_t s, LaunchFn launch, bool may_tune = true) {
-  const std::vector<int> slabs = slab_candidates(A.g);
   Shape choice{1, 0, 0, 1};
   if (const char* f = getenv("LQ_TUNE_FORCE")) {
     // testing hook: force "nr,order[,tpb,xcd]" (nr where it is a candidate, any valid traversal order)
@@ -450,6 +440,7 @@ static int tuned(lq_ctx* c, const std::string& key, Args& A, size_t out_bytes, i
     // coordinate search: columns per thread, traversal order, columns per
     // thread again at that order, then tiles per workgroup x block order, each
     // around the best shape so far
+    const std::vector<int> slabs = slab_candidates(A.g);
     for (int nr : nrs) trial(Shape{nr, 0, 0, 1});
     const Shape s0 = choice;
     for (int bz : slabs)

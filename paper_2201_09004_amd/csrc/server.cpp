@@ -76,6 +76,7 @@ class Engine {
     stp.reset();  // frees on the stream, which must still exist
     if (s) {
       hipStreamSynchronize(s);
+      work_stream_gone(ctx->device, s);
       hipStreamDestroy(s);
     }
   }

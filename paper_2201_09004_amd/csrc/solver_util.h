@@ -14,17 +14,11 @@ namespace lq {
 
 struct HostPinned {
   double* p = nullptr;
-  explicit HostPinned(size_t n) {
-    if (hipHostMalloc((void**)&p, n * sizeof(double), hipHostMallocDefault) != hipSuccess) {
-      (void)hipGetLastError();
-      p = nullptr;
-    }
-  }
+  size_t got = 0;
+  explicit HostPinned(size_t n) { p = pinned_alloc(n * sizeof(double), &got); }
   HostPinned(const HostPinned&) = delete;
   HostPinned& operator=(const HostPinned&) = delete;
-  ~HostPinned() {
-    if (p) hipHostFree(p);
-  }
+  ~HostPinned() { pinned_free(p, got); }
 };
 
 // per-column solver state [ncol][ST_STRIDE] on the device and in pinned host memory
@@ -33,8 +27,12 @@ struct State {
   HostPinned host;
   int ncol;
   hipStream_t s;
+  bool pushed = false;  // an upload from `host` may still be running
   State(int n, hipStream_t st)
       : dev((size_t)std::max(n, 1) * ST_STRIDE * 8, st), host((size_t)std::max(n, 1) * ST_STRIDE), ncol(n), s(st) {}
+  ~State() {
+    if (pushed) (void)hipStreamSynchronize(s);  // `host` goes to its next user
+  }
   bool ok() const { return dev.p && host.p; }
   double* d() { return dev.as<double>(); }
   double& h(int col, int k) { return host.p[col * ST_STRIDE + k]; }
@@ -43,12 +41,14 @@ struct State {
     if (hipMemcpyAsync(host.p, dev.p, cnt, hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
       return fail(LQ_EDEVICE, "state readback");
+    pushed = false;
     return 0;
   }
   int push(int n = -1) {
     const size_t cnt = (size_t)(n < 0 ? ncol : n) * ST_STRIDE * 8;
     if (hipMemcpyAsync(dev.p, host.p, cnt, hipMemcpyHostToDevice, s) != hipSuccess)
       return fail(LQ_EDEVICE, "state upload");
+    pushed = true;
     return 0;
   }
 };
