@@ -8,6 +8,8 @@
 // (wave butterfly, then waves in index order); the scalar kernels sum the
 // partials of a column in block order.  A column's result therefore does not
 // depend on which other columns share the batch.
+#include <algorithm>
+
 #include "lq_common.h"
 #include "lq_kernels.h"
 
@@ -339,9 +341,11 @@ int launch_scalar(int op, const double* partial, int gridx, int ncol, double* st
 
 // ------------------------------------------------------------ multi-shift CG
 // shift state [i][j][8]: 0 zeta, 1 zeta_old, 2 alpha_i, 3 beta_i, 4 active, 5 zeta_new
-// One iteration: ms_xr (r -= alpha A p and |r|^2, base columns only), the
-// beta step, then ms_p (x_i += alpha_i p_i and p_i = zeta_i r + beta_i p_i,
-// every shift: one pass over p_i serves both updates).
+// One iteration: ms_xr (r - alpha A p and its |.|^2, base columns only), the
+// beta step, then the directions and solutions.  Only the base direction is
+// needed by the next iteration (ms_p0); the other updates need the residual
+// and the iteration's scalars alone, so ms_p applies the iterations of up to
+// kMsSlots residuals in one pass over x_i and p_i.
 // base state (per rhs j): ST_ALPHA, ST_BETA, ST_RR, ST_AUX = alpha_old, ST_AUX+1 = beta_old, ST_RR0 = |b|^2,
 // ST_PAD = tol^2 of the multi-shift stage
 enum { MS_Z = 0, MS_ZO, MS_A, MS_B, MS_ACT, MS_ZN };
@@ -363,36 +367,117 @@ __global__ void __launch_bounds__(256) ms_xr_kernel(MsArgs A) {
     IOt::load(A.ap, bj, cb, q);
 #pragma unroll
     for (int k = 0; k < NC; ++k) r[k] = r[k] - a * q[k];
-    IOt::store(A.r, bj, cb, r);
-    IOt::load(A.r, bj, cb, r);
+    IOt::store(A.rnew, bj, cb, r);
+    IOt::load(A.rnew, bj, cb, r);
     red[0] += norm_acc<R, NC>(r);
   }
   block_reduce_store<1>(red, A.partial + ((int64_t)j * gridDim.x + blockIdx.x) * 4);
 }
 
 template <int P, int NC>
-__global__ void __launch_bounds__(256) ms_p_kernel(MsArgs A) {
+__global__ void __launch_bounds__(256) ms_p0_kernel(MsArgs A) {
   using R = typename RealOf<P>::T;
   using IOt = IO<P, NC>;
+  const int j = blockIdx.y;
+  const double* sh = A.hist + ((int64_t)(A.nslot - 1) * A.nshift * A.nrhs + j) * 4;
+  if (sh[3] == 0.0) return;
+  const R z = (R)sh[1], b = (R)sh[2];
+  const int64_t n = (int64_t)A.npar * A.Vh;
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
+    const int par = (int)(t / A.Vh);
+    const int cb = (int)(t - (int64_t)par * A.Vh);
+    const int64_t bj = (int64_t)j * A.npar + par;
+    cx<R> r[NC], p[NC];
+    IOt::load(A.r, bj, cb, r);
+    IOt::load(A.pw, bj, cb, p);
+#pragma unroll
+    for (int k = 0; k < NC; ++k) p[k] = z * r[k] + b * p[k];
+    IOt::store(A.pw, bj, cb, p);
+  }
+}
+
+// Bound by HBM: per shift column one read and one write of x_i and p_i for all
+// NS slots, and one read of each slot's residual per base column, held in
+// registers over the shifts (8 shifts x 8 slots: 5 column passes per iteration
+// against 33 when every iteration was applied by itself).  A column is taken
+// as a flat array of 16-byte elements, the next shift's p and x are loaded
+// while this one's are worked on.  24^3x64, 12 columns x 8 shifts, FP32: 812
+// us per iteration applied by itself, 1407 us for eight.
+// The arithmetic per element is that of one iteration after the other, so the
+// result is bitwise the same.
+template <typename R, int NS>
+__global__ void __launch_bounds__(256) ms_p_kernel(MsArgs A) {
+  constexpr int W = 16 / sizeof(R);
+  struct alignas(16) E { R v[W]; };
+  const int j = blockIdx.y;
+  // 16-byte elements of a column (Vh is a multiple of 8)
+  const int64_t n = (int64_t)A.npar * A.Vh * A.nc * 2 / W;
+  const int64_t hs = (int64_t)A.nshift * A.nrhs * 4;  // stride of a slot in hist
+  const E* R0[NS];
+#pragma unroll
+  for (int q = 0; q < NS; ++q) R0[q] = (const E*)A.rs[q < A.nslot ? q : 0].data + (int64_t)j * n;
+  E* P0 = (E*)A.p.data + (int64_t)j * n;
+  E* X0 = (E*)A.x.data + (int64_t)j * n;
+  const int64_t step = (int64_t)A.nrhs * n;  // from shift to shift
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
+    E p = P0[t], x = X0[t], r[NS];
+#pragma unroll
+    for (int q = 0; q < NS; ++q) r[q] = R0[q][t];
+    for (int i = 0; i < A.nshift; ++i) {
+      E pn = p, xn = x;
+      if (i + 1 < A.nshift) {
+        pn = P0[(i + 1) * step + t];
+        xn = X0[(i + 1) * step + t];
+      }
+      const double* h0 = A.hist + ((int64_t)i * A.nrhs + j) * 4;
+      // alpha_i is zero for shifts inactive at an iteration's alpha step; a
+      // shift retired by an iteration's beta step still takes its x step
+      bool xs = false, ps = false;
+#pragma unroll
+      for (int q = 0; q < NS; ++q) {
+        if (q >= A.nslot) continue;
+        const double* h = h0 + q * hs;
+        const R ai = (R)h[0], z = (R)h[1], b = (R)h[2];
+        if (h[0] != 0.0) {
+          xs = true;
+#pragma unroll
+          for (int k = 0; k < W; ++k) x.v[k] = x.v[k] + ai * p.v[k];
+        }
+        if (h[3] != 0.0) {
+          ps = true;
+#pragma unroll
+          for (int k = 0; k < W; ++k) p.v[k] = z * r[q].v[k] + b * p.v[k];
+        }
+      }
+      if (xs) X0[i * step + t] = x;
+      if (ps) P0[i * step + t] = p;
+      p = pn;
+      x = xn;
+    }
+  }
+}
+
+// the same for one iteration in FP16 storage (values with a norm per site)
+template <int NC>
+__global__ void __launch_bounds__(256) ms_p16_kernel(MsArgs A) {
+  using IOt = IO<16, NC>;
   const int j = blockIdx.y;
   const int64_t n = (int64_t)A.npar * A.Vh;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
     const int par = (int)(t / A.Vh);
     const int cb = (int)(t - (int64_t)par * A.Vh);
-    cx<R> r[NC];
-    IOt::load(A.r, (int64_t)j * A.npar + par, cb, r);
+    cx<float> r[NC];
+    IOt::load(A.rs[0], (int64_t)j * A.npar + par, cb, r);
     for (int i = 0; i < A.nshift; ++i) {
-      const double* sh = A.sh + ((int64_t)i * A.nrhs + j) * 8;
-      // alpha_i is zero for shifts inactive at this iteration's alpha step; a
-      // shift retired by this iteration's beta step still takes its x step
-      const bool xs = sh[MS_A] != 0.0, ps = sh[MS_ACT] != 0.0;
+      const double* h = A.hist + ((int64_t)i * A.nrhs + j) * 4;
+      const bool xs = h[0] != 0.0, ps = h[3] != 0.0;
       if (!xs && !ps) continue;
-      const R ai = (R)sh[MS_A], z = (R)sh[MS_Z], b = (R)sh[MS_B];
+      const float ai = (float)h[0], z = (float)h[1], b = (float)h[2];
       const int64_t bi = ((int64_t)i * A.nrhs + j) * A.npar + par;
-      cx<R> p[NC];
+      cx<float> p[NC];
       IOt::load(A.p, bi, cb, p);
       if (xs) {
-        cx<R> x[NC];
+        cx<float> x[NC];
         IOt::load(A.x, bi, cb, x);
 #pragma unroll
         for (int k = 0; k < NC; ++k) x[k] = x[k] + ai * p[k];
@@ -466,6 +551,14 @@ __global__ void ms_beta_kernel(MsArgs A) {
   bool any = false;
   for (int i = 1; i < A.nshift; ++i) any |= A.sh[((int64_t)i * A.nrhs + j) * 8 + MS_ACT] != 0.0;
   if (rr < tol2 && !any) A.sh[(int64_t)j * 8 + MS_ACT] = 0.0;
+  for (int i = 0; i < A.nshift; ++i) {
+    const double* sh = A.sh + ((int64_t)i * A.nrhs + j) * 8;
+    double* h = A.hist + (((int64_t)(A.nslot - 1) * A.nshift + i) * A.nrhs + j) * 4;
+    h[0] = sh[MS_A];
+    h[1] = sh[MS_Z];
+    h[2] = sh[MS_B];
+    h[3] = sh[MS_ACT];
+  }
   s[ST_AUX] = s[ST_ALPHA];
   s[ST_AUX + 1] = b;
   s[ST_BETA] = b;
@@ -509,8 +602,24 @@ int launch_ms_xr(const MsArgs& A, hipStream_t s) {
   LQ_MS_DISPATCH(ms_xr_kernel);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
+int launch_ms_p0(const MsArgs& A, hipStream_t s) {
+  LQ_MS_DISPATCH(ms_p0_kernel);
+  return hipGetLastError() == hipSuccess ? 0 : -3;
+}
 int launch_ms_p(const MsArgs& A, hipStream_t s) {
-  LQ_MS_DISPATCH(ms_p_kernel);
+  if (A.nslot < 1 || A.nslot > kMsSlots || (A.prec == 16 && A.nslot > 1)) return -1;
+  const int64_t n = (int64_t)A.npar * A.Vh * A.nc / (A.prec == 64 ? 1 : 2);  // 16-byte elements of a column
+  const dim3 grid(A.prec == 16 ? A.gridx : (int)std::min<int64_t>((n + 255) / 256, 4096), A.nrhs), block(256);
+  if (A.prec == 16) {
+    if (A.nc == 12) ms_p16_kernel<12><<<grid, block, 0, s>>>(A);
+    else ms_p16_kernel<3><<<grid, block, 0, s>>>(A);
+  } else if (A.prec == 32) {
+    if (A.nslot == 1) ms_p_kernel<float, 1><<<grid, block, 0, s>>>(A);
+    else ms_p_kernel<float, kMsSlots><<<grid, block, 0, s>>>(A);
+  } else {
+    if (A.nslot == 1) ms_p_kernel<double, 1><<<grid, block, 0, s>>>(A);
+    else ms_p_kernel<double, kMsSlots><<<grid, block, 0, s>>>(A);
+  }
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 int launch_ms_scalar_alpha(const MsArgs& A, const double* sigma, hipStream_t s) {

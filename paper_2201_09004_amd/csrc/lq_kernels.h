@@ -131,17 +131,27 @@ enum { SC_CG_ALPHA = 0, SC_CG_BETA, SC_BICG_ALPHA, SC_BICG_OMEGA, SC_BICG_BETA, 
        SC_DOT_TO_AUX };
 int launch_scalar(int op, const double* partial, int gridx, int ncol, double* st, hipStream_t s);
 
-// multi-shift CG (Jegerlehner): fields with ncol = nshift * nrhs, shift-major
+// multi-shift CG (Jegerlehner): fields with ncol = nshift * nrhs, shift-major.
+// x_i and p_i are updated from the residuals of up to kMsSlots iterations at
+// once: `r` holds the newest residual, rs[0 .. nslot) those of the iterations
+// not yet applied (oldest first), hist their shift scalars.
+constexpr int kMsSlots = 8;
 struct MsArgs {
   int prec, nc, nrhs, nshift, npar, Vh;
   FieldRef x, p, r, ap;
+  FieldRef rnew;           // ms_xr writes the new residual here (may be r)
+  FieldRef pw;             // ms_p0: the base direction the operator is applied to
+  FieldRef rs[kMsSlots];
+  int nslot;               // ms_p: iterations to apply; the beta step records its scalars in slot nslot - 1
+  double* hist;            // [kMsSlots][nshift][nrhs][4]: alpha_i, zeta_i, beta_i, active
   double* sh;  // shift state [nshift][nrhs][8]
   double* st;  // base state [nrhs][ST_STRIDE]
   double* partial;
   int gridx;
 };
-int launch_ms_xr(const MsArgs& A, hipStream_t s);     // r -= a Ap ; red |r|^2
-int launch_ms_p(const MsArgs& A, hipStream_t s);      // x_i += a_i p_i ; p_i = z_i r + b_i p_i (p_0: z = 1)
+int launch_ms_xr(const MsArgs& A, hipStream_t s);     // rnew = r - a Ap ; red |rnew|^2
+int launch_ms_p0(const MsArgs& A, hipStream_t s);     // pw = r + b pw, base columns
+int launch_ms_p(const MsArgs& A, hipStream_t s);      // per slot: x_i += a_i p_i ; p_i = z_i r + b_i p_i (p_0: z = 1)
 int launch_ms_scalar_alpha(const MsArgs& A, const double* sigma, hipStream_t s);
 int launch_ms_scalar_beta(const MsArgs& A, hipStream_t s);
 int launch_ms_init(const MsArgs& A, hipStream_t s);

@@ -41,14 +41,15 @@ static bool verbose() {
 }
 
 // timing records of the multi-shift vector kernels with their algorithmic
-// bytes: ms_xr reads r and A p and writes r (base columns); ms_p reads r once
-// and, per shift column, reads p and x and writes both
+// bytes: ms_xr reads r and A p and writes r (base columns); ms_p reads the
+// residual of each iteration it applies and, per shift column, reads p and x
+// and writes both
 struct MsProf {
   Prof all, one;
   char name[32];
   static double bytes(const MsArgs& M, bool p) {
     const double sb = (double)site_bytes(M.prec, M.nc) + (sep_norm(M.prec, M.nc) ? 4 : 0);
-    const double cols = p ? M.nrhs + 4.0 * M.nshift * M.nrhs : 3.0 * M.nrhs;
+    const double cols = p ? (M.nslot + 4.0 * M.nshift) * M.nrhs : 3.0 * M.nrhs;
     return cols * M.npar * M.Vh * sb;
   }
   MsProf(lq_ctx* c, const MsArgs& M, bool p, hipStream_t s)
@@ -1153,7 +1154,10 @@ static int overlap_solve(OpEnv& env, const lq_params* prm, int n_rhs, const doub
       if ((e = blas_prepare(c, blr, g, 2, ncs, s))) return e;
       MsArgs M{};
       M.prec = pms; M.nc = 12; M.nrhs = nsec; M.nshift = nm; M.npar = 2; M.Vh = g.Vh;
-      M.x = xm.f; M.p = p.f; M.r = rr.f; M.ap = ap.f;
+      DBuf hist(sizeof(double) * 4 * ncs, s);
+      if (!hist.p) return fail(LQ_ENOMEM, "overlap multi-shift buffers");
+      M.x = xm.f; M.p = p.f; M.r = M.rnew = M.rs[0] = rr.f; M.ap = ap.f;
+      M.hist = hist.as<double>(); M.nslot = 1;
       M.sh = sh.as<double>(); M.st = st.d(); M.partial = blr.partial; M.gridx = blr.gridx;
       if ((e = blr.op(OP_NORM2, &rr))) return e;
       if (launch_ms_init(M, s)) return fail(LQ_EDEVICE, "ms init");
@@ -1468,7 +1472,24 @@ int solve(lq_ctx* c, const lq_action* act, lq_field* f, const lq_params* prm, in
       // solve against 6.5 s for FP16 to 2e-3, 5.7 s for 1e-5, 4.8 s for 1e-6
       // and 1e-7, 4.5 s for 1e-9).
       const int pms = plo == 16 ? LQ_MS_PREC16 : plo;
-      Vec r = make_vec(g, pms, 3, n_rhs, 1, 0, s);
+      // residuals of the iterations whose x_i and p_i updates are still to be
+      // applied, in turn (FP16 storage applies every iteration by itself, and
+      // fewer are kept where memory is short)
+      std::vector<Vec> ring;
+      const int want = pms == 16 ? 1 : kMsSlots + 1;
+      for (int k = 0; k < want; ++k) {
+        ring.push_back(make_vec(g, pms, 3, n_rhs, 1, 0, s));
+        if (!ring.back().ok()) {
+          ring.pop_back();
+          break;
+        }
+      }
+      // one residual in place, or the newest and those of nslot iterations
+      const int nslot = std::max(1, (int)ring.size() - 1);
+      const bool lazy = ring.size() > 2;
+      if (ring.empty()) return fail(LQ_ENOMEM, "multi-shift buffers");
+      ring.resize(lazy ? nslot + 1 : 1);
+      Vec& r = ring[0];
       Vec ap = make_vec(g, pms, 3, n_rhs, 1, 0, s);
       Vec to = make_vec(g, pms, 3, n_rhs, 1, 1, s);
       Vec p = make_vec(g, pms, 3, ncol, 1, 0, s);
@@ -1496,27 +1517,53 @@ int solve(lq_ctx* c, const lq_action* act, lq_field* f, const lq_params* prm, in
       if ((e = blr.op(OP_NORM2, &r))) return e;
       if (launch_ms_init(M, s)) return fail(LQ_EDEVICE, "ms init");
       std::vector<double> hsh((size_t)8 * ncol);
-      Vec p0 = view(p, 0, n_rhs);
+      // the direction the operator is applied to: column set 0 of p, or with
+      // deferred updates a copy ahead of it
+      Vec pw;
+      if (lazy) {
+        pw = make_vec(g, pms, 3, n_rhs, 1, 0, s);
+        if (!pw.ok()) return fail(LQ_ENOMEM, "multi-shift buffers");
+        if ((e = vec_copy(pw, r))) return e;
+      }
+      Vec p0 = lazy ? view(pw, 0, n_rhs) : view(p, 0, n_rhs);
+      DBuf hist(sizeof(double) * 4 * ncol * nslot, s);
+      if (!hist.p) return fail(LQ_ENOMEM, "multi-shift scalars");
+      M.pw = p0.f;
+      M.hist = hist.as<double>();
       // <p_0, A p_0> from the stencil epilogue: partials over 64-site tiles
       const int mtiles = (g.Vh + 63) / 64;
       DBuf mred(sizeof(double) * 4 * (size_t)mtiles * n_rhs, s);
       if (!mred.p) return fail(LQ_ENOMEM, "multi-shift partials");
-      MsArgs Ma = M;
-      Ma.partial = mred.as<double>();
-      Ma.gridx = mtiles;
-      int it = 0;
+      int it = 0, waiting = 0;  // waiting: iterations whose x_i, p_i updates are deferred
+      // x_i and p_i of the waiting iterations
+      auto flush = [&]() -> int {
+        if (!waiting) return 0;
+        MsProf pr(c, M, true, s);
+        if (launch_ms_p(M, s)) return fail(LQ_EDEVICE, "ms p");
+        waiting = 0;
+        return 0;
+      };
       for (; it < maxiter; ++it) {
         if ((e = stag_normal_even(env, pms, ap, p0, to, nullptr, m0 * m0, mred.as<double>()))) return e;
+        const Vec& r0 = ring[lazy ? it % (nslot + 1) : 0];
+        const Vec& r1 = ring[lazy ? (it + 1) % (nslot + 1) : 0];
+        M.r = r0.f;
+        M.rnew = M.rs[waiting] = r1.f;
+        M.nslot = ++waiting;
+        MsArgs Ma = M;
+        Ma.partial = mred.as<double>();
+        Ma.gridx = mtiles;
         if (launch_ms_scalar_alpha(Ma, dsig.as<double>(), s)) return fail(LQ_EDEVICE, "ms alpha");
         {
           MsProf pr(c, M, false, s);
           if (launch_ms_xr(M, s)) return fail(LQ_EDEVICE, "ms xr");
         }
         if (launch_ms_scalar_beta(M, s)) return fail(LQ_EDEVICE, "ms beta");
-        {
-          MsProf pr(c, M, true, s);
-          if (launch_ms_p(M, s)) return fail(LQ_EDEVICE, "ms p");
+        if (lazy) {
+          M.r = r1.f;
+          if (launch_ms_p0(M, s)) return fail(LQ_EDEVICE, "ms p0");
         }
+        if (waiting == nslot && (e = flush())) return e;
         if ((it & 3) == 3 || it < 4) {
           hipMemcpyAsync(hsh.data(), sh.p, sizeof(double) * 8 * ncol, hipMemcpyDeviceToHost, s);
           if ((e = st.pull())) return e;
@@ -1527,6 +1574,7 @@ int solve(lq_ctx* c, const lq_action* act, lq_field* f, const lq_params* prm, in
           if (!any) break;
         }
       }
+      if ((e = flush())) return e;
       cnt.iters += it;
       if ((e = vec_copy(y, xm))) return e;
     }
