@@ -243,6 +243,32 @@ __device__ __forceinline__ cx<double> cdiv(cx<double> a, cx<double> b) {
 }
 __device__ __forceinline__ bool finite_c(cx<double> a) { return isfinite(a.re) && isfinite(a.im); }
 
+// the scalar steps of CG
+struct CgAlpha {
+  double a;
+  bool refused, bad;
+};
+// <p, A p> <= 0 can only come from rounding in low-precision storage (A is
+// positive definite): no step, and the column's direction is restarted by the
+// beta step; a non-finite value is a numeric error
+__device__ __forceinline__ CgAlpha cg_alpha(const double* s, double pap) {
+  const bool active = s[ST_ACTIVE] != 0.0;
+  CgAlpha c{s[ST_RR] / pap, false, false};
+  if (!isfinite(pap)) {
+    c.bad = true;
+    c.a = 0;
+  } else if (!(pap > 0.0) || !isfinite(c.a)) {
+    c.refused = active;
+    c.a = 0;
+  }
+  if (!active) c.a = 0;
+  return c;
+}
+__device__ __forceinline__ double cg_beta(double rr_old, double rr, bool refused, bool active) {
+  const double b = rr / rr_old;
+  return isfinite(b) && !refused && active ? b : 0.0;
+}
+
 __global__ void scalar_kernel(int op, const double* partial, int gridx, int ncol, double* st) {
   const int col = blockIdx.x;
   if (col >= ncol) return;
@@ -259,36 +285,26 @@ __global__ void scalar_kernel(int op, const double* partial, int gridx, int ncol
   auto getc = [&](int off) { return cx<double>{s[off], s[off + 1]}; };
   switch (op) {
     case SC_CG_ALPHA: {
-      // <p, A p> <= 0 can only come from rounding in low-precision storage
-      // (A is positive definite): flag a restart of the column (flag 1) and
-      // take no step; a non-finite value is a numeric error (flag 2)
-      const double pap = r0;
-      double a = s[ST_RR] / pap;
-      if (!isfinite(pap)) {
-        s[ST_FLAG] = 2;
-        a = 0;
-      } else if (!(pap > 0.0) || !isfinite(a)) {
-        if (active) s[ST_FLAG] = 1;
-        a = 0;
-      }
-      setc(ST_ALPHA, {active ? a : 0.0, 0.0});
+      const CgAlpha c = cg_alpha(s, r0);
+      if (c.bad) s[ST_FLAG] = 2;
+      else if (c.refused) s[ST_FLAG] = 1;
+      setc(ST_ALPHA, {c.a, 0.0});
+      s[ST_RROLD] = s[ST_RR];
+      s[ST_REFUSED] = c.refused;
       break;
     }
     case SC_CG_BETA: {
-      const double rr = r0;
-      double b = rr / s[ST_RR];
-      if (!isfinite(rr)) s[ST_FLAG] = 2;
-      if (!isfinite(b)) b = 0;
-      if (s[ST_FLAG] == 1) {
-        // the column took no step (SC_CG_ALPHA lost positivity): restart its
-        // direction with p = r, here on the device, so that iterations whose
-        // state the host does not read restart as well
-        b = 0;
+      // the column took no step (SC_CG_ALPHA lost positivity): restart its
+      // direction with p = r, here on the device, so that iterations whose
+      // state the host does not read restart as well
+      if (!isfinite(r0)) s[ST_FLAG] = 2;
+      const bool refused = s[ST_FLAG] == 1;
+      if (refused) {
         s[ST_FLAG] = 0;
         s[ST_NRST] += 1;
       }
-      setc(ST_BETA, {active ? b : 0.0, 0.0});
-      s[ST_RR] = rr;
+      setc(ST_BETA, {cg_beta(s[ST_RR], r0, refused, active), 0.0});
+      s[ST_RR] = r0;
       break;
     }
     case SC_BICG_ALPHA: {
@@ -336,6 +352,171 @@ __global__ void scalar_kernel(int op, const double* partial, int gridx, int ncol
 int launch_scalar(int op, const double* partial, int gridx, int ncol, double* st, hipStream_t s) {
   if (ncol == 0) return 0;
   scalar_kernel<<<ncol, kScalarThreads, 0, s>>>(op, partial, gridx, ncol, st);
+  return hipGetLastError() == hipSuccess ? 0 : -3;
+}
+
+// ------------------------------------------------------------ CG vectors
+// An iteration is two kernels around its scalar steps: r -= alpha q with
+// |r|^2, then x += alpha p and p = r + beta p together (8 column passes; x with
+// the first kernel's update, as it was, makes 9).  On large vectors both are
+// bound by HBM and the scalar steps run as kernels of their own.  Where the
+// partials are few (kCgFold) every workgroup sums them itself at its start,
+// and the one of block 0 records the scalars, which no workgroup of the same
+// launch reads: a launch of 3-4 us and the gap before it are saved per step.
+// FP32 and FP64 columns are taken as flat arrays of 16-byte elements, so that
+// 4096 sites make 192 workgroups instead of 16; FP16 sites carry their norm and
+// stay whole.  8^4, FP64, one column: 22 us of vector and scalar kernels per
+// iteration -> 7.0 us; 24^3x64, 96 columns, FP16 staggered: 1100 -> 972 us.
+template <typename R> struct alignas(16) Elem { R v[16 / sizeof(R)]; };
+
+int cg_grid(int prec, int nc, int npar, int Vh) {
+  const int64_t n = prec == 16 ? (int64_t)npar * Vh : (int64_t)npar * Vh * nc / (prec == 64 ? 1 : 2);
+  return (int)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 512));
+}
+
+template <int P, int NC>
+__global__ void __launch_bounds__(kScalarThreads) cg_r_kernel(CgArgs A) {
+  using R = typename RealOf<P>::T;
+  const int col = blockIdx.y;
+  double* s = A.st + (int64_t)col * ST_STRIDE;
+  double alpha;
+  if (A.fold) {
+    const CgAlpha c = cg_alpha(s, sum_r(A.pin + (int64_t)col * A.nin * 4, A.nin, 0));
+    alpha = c.a;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      if (c.bad) s[ST_FLAG] = 2;
+      else if (c.refused) s[ST_FLAG] = 1;
+      s[ST_ALPHA] = c.a;
+      s[ST_ALPHA + 1] = 0.0;
+      s[ST_RROLD] = s[ST_RR];
+      s[ST_REFUSED] = c.refused;
+    }
+  } else {
+    alpha = s[ST_ALPHA];
+  }
+  const R a = (R)alpha;
+  double red[1] = {0.0};
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  if constexpr (P == 16) {
+    const int64_t n = (int64_t)A.npar * A.Vh;
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += step) {
+      const int par = (int)(t / A.Vh), cb = (int)(t - (int64_t)par * A.Vh);
+      const int64_t blk = (int64_t)col * A.npar + par;
+      cx<R> r[NC], q[NC];
+      IO<P, NC>::load(A.r, blk, cb, r);
+      IO<P, NC>::load(A.q, blk, cb, q);
+#pragma unroll
+      for (int k = 0; k < NC; ++k) r[k] = r[k] - a * q[k];
+      IO<P, NC>::store(A.r, blk, cb, r);
+      IO<P, NC>::load(A.r, blk, cb, r);  // reduce what was stored (rounded)
+      red[0] += norm_acc<R, NC>(r);
+    }
+  } else {
+    using E = Elem<R>;
+    constexpr int W = 16 / sizeof(R);
+    const int64_t n = (int64_t)A.npar * A.Vh * NC * 2 / W;
+    E* r0 = (E*)A.r.data + (int64_t)col * n;
+    const E* q0 = (const E*)A.q.data + (int64_t)col * n;
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += step) {
+      E r = r0[t];
+      const E q = q0[t];
+#pragma unroll
+      for (int k = 0; k < W; ++k) {
+        r.v[k] = r.v[k] - a * q.v[k];
+        red[0] += (double)r.v[k] * (double)r.v[k];
+      }
+      r0[t] = r;
+    }
+  }
+  block_reduce_store<1>(red, A.pout + ((int64_t)col * gridDim.x + blockIdx.x) * 4);
+}
+
+template <int P, int NC>
+__global__ void __launch_bounds__(kScalarThreads) cg_px_kernel(CgArgs A) {
+  using R = typename RealOf<P>::T;
+  const int col = blockIdx.y;
+  double* s = A.st + (int64_t)col * ST_STRIDE;
+  double beta;
+  if (A.fold) {
+    const double rr = sum_r(A.pin + (int64_t)col * A.nin * 4, A.nin, 0);
+    const bool refused = s[ST_REFUSED] != 0.0;
+    beta = cg_beta(s[ST_RROLD], rr, refused, s[ST_ACTIVE] != 0.0);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      if (!isfinite(rr)) {
+        s[ST_FLAG] = 2;
+      } else if (refused && s[ST_FLAG] == 1) {
+        s[ST_FLAG] = 0;
+        s[ST_NRST] += 1;
+      }
+      s[ST_BETA] = beta;
+      s[ST_BETA + 1] = 0.0;
+      s[ST_RR] = rr;
+    }
+  } else {
+    beta = s[ST_BETA];
+  }
+  const R a = (R)s[ST_ALPHA], b = (R)beta;
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  if constexpr (P == 16) {
+    const int64_t n = (int64_t)A.npar * A.Vh;
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += step) {
+      const int par = (int)(t / A.Vh), cb = (int)(t - (int64_t)par * A.Vh);
+      const int64_t blk = (int64_t)col * A.npar + par;
+      cx<R> p[NC], x[NC], r[NC];
+      IO<P, NC>::load(A.p, blk, cb, p);
+      IO<P, NC>::load(A.x, blk, cb, x);
+      IO<P, NC>::load(A.r, blk, cb, r);
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        x[k] = x[k] + a * p[k];
+        p[k] = r[k] + b * p[k];
+      }
+      IO<P, NC>::store(A.x, blk, cb, x);
+      IO<P, NC>::store(A.p, blk, cb, p);
+    }
+  } else {
+    using E = Elem<R>;
+    constexpr int W = 16 / sizeof(R);
+    const int64_t n = (int64_t)A.npar * A.Vh * NC * 2 / W;
+    E* p0 = (E*)A.p.data + (int64_t)col * n;
+    E* x0 = (E*)A.x.data + (int64_t)col * n;
+    const E* r0 = (const E*)A.r.data + (int64_t)col * n;
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += step) {
+      E p = p0[t], x = x0[t];
+      const E r = r0[t];
+#pragma unroll
+      for (int k = 0; k < W; ++k) {
+        x.v[k] = x.v[k] + a * p.v[k];
+        p.v[k] = r.v[k] + b * p.v[k];
+      }
+      x0[t] = x;
+      p0[t] = p;
+    }
+  }
+}
+
+#define LQ_CG_DISPATCH(KER)                                                               \
+  do {                                                                                    \
+    const dim3 grid(A.gridx, A.ncol), block(kScalarThreads);                              \
+    if (A.nc == 12) {                                                                     \
+      if (A.prec == 64) KER<64, 12><<<grid, block, 0, s>>>(A);                            \
+      else if (A.prec == 32) KER<32, 12><<<grid, block, 0, s>>>(A);                       \
+      else KER<16, 12><<<grid, block, 0, s>>>(A);                                         \
+    } else {                                                                              \
+      if (A.prec == 64) KER<64, 3><<<grid, block, 0, s>>>(A);                             \
+      else if (A.prec == 32) KER<32, 3><<<grid, block, 0, s>>>(A);                        \
+      else KER<16, 3><<<grid, block, 0, s>>>(A);                                          \
+    }                                                                                     \
+  } while (0)
+
+int launch_cg_r(const CgArgs& A, hipStream_t s) {
+  if (A.ncol == 0) return 0;
+  LQ_CG_DISPATCH(cg_r_kernel);
+  return hipGetLastError() == hipSuccess ? 0 : -3;
+}
+int launch_cg_px(const CgArgs& A, hipStream_t s) {
+  if (A.ncol == 0) return 0;
+  LQ_CG_DISPATCH(cg_px_kernel);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
@@ -407,8 +588,8 @@ __global__ void __launch_bounds__(256) ms_p0_kernel(MsArgs A) {
 // result is bitwise the same.
 template <typename R, int NS>
 __global__ void __launch_bounds__(256) ms_p_kernel(MsArgs A) {
+  using E = Elem<R>;
   constexpr int W = 16 / sizeof(R);
-  struct alignas(16) E { R v[W]; };
   const int j = blockIdx.y;
   // 16-byte elements of a column (Vh is a multiple of 8)
   const int64_t n = (int64_t)A.npar * A.Vh * A.nc * 2 / W;

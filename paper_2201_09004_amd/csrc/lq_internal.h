@@ -228,7 +228,8 @@ int ensure_clover(OpEnv& e, int prec);
 const Clover* get_clover(OpEnv& e);
 
 // Wilson-type: full-lattice D, D^dag, hop; site terms; Schur operator and helpers
-int wilson_D(OpEnv& e, int prec, Vec& out, const Vec& in, bool dag);
+// red (Wilson action, not dagger): |out|^2 per column as partials over 64-site tiles, [col][tile][4], the first of four
+int wilson_D(OpEnv& e, int prec, Vec& out, const Vec& in, bool dag, double* red = nullptr);
 int wilson_hop(OpEnv& e, int prec, Vec& out, const Vec& in);
 int tm_site(OpEnv& e, int prec, Vec& out, const Vec& in, bool inverse);
 // red_mode 2: the partials of <out, in> and |out|^2 are written to red as

@@ -15,8 +15,9 @@ namespace lq {
 // |out|^2 written as wave partials red[(col * ntile + tile) * 4 + k]
 // (ntile = 64-site tiles of the launch).  EPI_CLOVINV_XPAY: A^{-1} (x + k hop)
 // (the even-odd source and the odd-site reconstruction of the twisted clover).
+// EPI_XPAY_NORM: EPI_XPAY plus |out|^2 per column in red[... + 0].
 enum { EPI_HOP = 0, EPI_XPAY, EPI_XPAY_G5, EPI_CLOVINV, EPI_XMY_CLOVINV, EPI_SITE, EPI_CHEB, EPI_XMY_RTS,
-       EPI_CLOVINV_XPAY };
+       EPI_CLOVINV_XPAY, EPI_XPAY_NORM };
 
 struct WilsonArgs {
   Geom g;
@@ -33,7 +34,7 @@ struct WilsonArgs {
   const void* clov_inv;  // full complex A^{-1} per chirality
   const double* acol;    // per-column coefficient of x (or nullptr: use a)
   double a, k_hop, mu_tw, s1, ck, s2;
-  double* red;           // fused-reduction partials (EPI_XMY_RTS)
+  double* red;           // fused-reduction partials (EPI_XMY_RTS, EPI_XPAY_NORM)
 };
 int launch_wilson(const WilsonArgs& A, hipStream_t s);
 template <int P>
@@ -89,7 +90,7 @@ enum {
   OP_AXPY = 0,   // f1 += c0 * f0
   OP_AXMY,       // f1 -= c0 * f0
   OP_XPAY,       // f1 = f0 + c0 * f1
-  OP_CG,         // f2 += c0 f0 ; f3 -= c0 f1 ; red |f3|^2
+  OP_CG,         // f2 += c0 f0 ; f3 -= c0 f1 ; red |f3|^2  (serving engine)
   OP_BICG_XR,    // f3 += c0 f0 + c1 f1 ; f1 = f1 - c1 f2 ; red <f4,f1>, |f1|^2   (c0=alpha, c1=omega)
   OP_BICG_P,     // f2 = f0 + c0 (f2 - c1 f1)                                     (c0=beta, c1=omega)
   OP_DOT,        // red <f0, f1>
@@ -106,7 +107,10 @@ enum {
 };
 
 constexpr int ST_STRIDE = 16;  // doubles of solver state per column
-// ST_NRST: CG direction restarts after a loss of positivity of <p, A p>
+// ST_NRST: CG direction restarts after a loss of positivity of <p, A p>.
+// CG keeps |r|^2 of before its alpha step (ST_RROLD) and whether that step was
+// refused (ST_REFUSED) where BiCGStab keeps rho.
+enum { ST_RROLD = 0, ST_REFUSED = 1 };
 enum { ST_RHO = 0, ST_ALPHA = 2, ST_OMEGA = 4, ST_BETA = 6, ST_RR = 8, ST_FLAG = 9, ST_ACTIVE = 10, ST_AUX = 11,
        ST_RR0 = 13, ST_PAD = 14, ST_NRST = 15 };
 
@@ -122,6 +126,21 @@ struct BlasArgs {
 };
 int launch_blas(const BlasArgs& A, hipStream_t s);
 int blas_gridx(int64_t nsite);
+
+// the two vector kernels of a CG iteration, scalars included where the partials are few
+struct CgArgs {
+  int prec, nc, ncol, npar, Vh;
+  FieldRef p, q, x, r;
+  double* st;
+  const double* pin;  // fold: partials [ncol][nin][4] of <p, A p> (cg_r) or |r|^2 (cg_px)
+  int nin;
+  double* pout;       // cg_r: partials [ncol][gridx][4] of |r|^2
+  int gridx;          // cg_grid
+  int fold;           // 1: the scalar step (SC_CG_ALPHA, SC_CG_BETA) from pin first, 0: scalars from st
+};
+int cg_grid(int prec, int nc, int npar, int Vh);
+int launch_cg_r(const CgArgs& A, hipStream_t s);   // r -= alpha q ; |r|^2
+int launch_cg_px(const CgArgs& A, hipStream_t s);  // x += alpha p ; p = r + beta p
 
 // y(prec_y) += x(prec_x) element-wise, both with the same shape
 int launch_axpy_mixed(FieldRef y, int py, FieldRef x, int px, int nc, int ncol, int npar, int Vh, hipStream_t s);

@@ -494,14 +494,15 @@ static int run_wilson(OpEnv& e, WilsonArgs& A, int n_fields, int clov_mats, int 
   A.recon = (e.recon && A.prec != 64) ? 1 : 0;
   if (!A.links) return fail(LQ_EDEVICE, "links not packed");
   const int nsite = A.par_out == 2 ? 2 * A.g.Vh : A.g.Vh;
-  static const char* epi_names[] = {"hop", "xpay", "xpay_g5", "clovinv", "xmy", "site", "cheb", "xmyt", "clovinv_x"};
+  static const char* epi_names[] = {"hop", "xpay", "xpay_g5", "clovinv", "xmy", "site", "cheb", "xmyt", "clovinv_x",
+                                    "xpayn"};
   char name[48];
   snprintf(name, sizeof(name), "wilson%d_%s", A.prec, epi_names[A.epi]);
   char key[160];
   snprintf(key, sizeof(key), "%s_r%d_d%d_n%d_v%d_p%d", name, A.recon, A.dag, col_bucket(A.ncol), A.g.Vh, A.par_out);
   const bool blocked = !A.dag && (A.epi == EPI_CLOVINV || A.epi == EPI_XMY_CLOVINV || A.epi == EPI_XPAY ||
                                   A.epi == EPI_XPAY_G5 || A.epi == EPI_CHEB || A.epi == EPI_XMY_RTS ||
-                                  A.epi == EPI_SITE || A.epi == EPI_CLOVINV_XPAY);
+                                  A.epi == EPI_SITE || A.epi == EPI_CLOVINV_XPAY || A.epi == EPI_XPAY_NORM);
   const int out_npar = A.out.npar;
   // timed under the kernel's name and under name_n<columns> (solvers that drop
   // converged columns launch the same kernel at several widths)
@@ -521,7 +522,7 @@ static int run_wilson(OpEnv& e, WilsonArgs& A, int n_fields, int clov_mats, int 
 }
 
 // ------------------------------------------------------------------ Wilson type
-int wilson_D(OpEnv& e, int prec, Vec& out, const Vec& in, bool dag) {
+int wilson_D(OpEnv& e, int prec, Vec& out, const Vec& in, bool dag, double* red) {
   int r = ensure_links(e, prec);
   if (r) return r;
   WilsonArgs A{};
@@ -542,9 +543,10 @@ int wilson_D(OpEnv& e, int prec, Vec& out, const Vec& in, bool dag) {
     A.mu_tw = dag ? -e.act.mu : e.act.mu;
     return run_wilson(e, A, 3, 1, 504);
   }
-  A.epi = EPI_XPAY;
+  A.epi = red ? EPI_XPAY_NORM : EPI_XPAY;
+  A.red = red;
   A.a = 4.0 + e.act.m;
-  return run_wilson(e, A, 3, 0, 48);
+  return run_wilson(e, A, 3, 0, red ? 96 : 48);
 }
 
 int wilson_hop(OpEnv& e, int prec, Vec& out, const Vec& in) {

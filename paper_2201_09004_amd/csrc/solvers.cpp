@@ -57,6 +57,24 @@ struct MsProf {
         one(c, (snprintf(name, sizeof(name), "ms%d_%s", M.prec, p ? "p" : "xr"), name), s, bytes(M, p)) {}
 };
 
+// timing records of the CG vector kernels with their algorithmic bytes
+struct CgProf {
+  Prof all, one;
+  char name[32];
+  static double bytes(const CgArgs& A, bool px) {
+    return (double)A.ncol * A.npar * A.Vh * (px ? 5 : 3) * (site_bytes(A.prec, A.nc) + (sep_norm(A.prec, A.nc) ? 4 : 0));
+  }
+  CgProf(lq_ctx* c, const CgArgs& A, bool px, hipStream_t s)
+      : all(c, "blas", s, bytes(A, px)),
+        one(c, (snprintf(name, sizeof(name), "cg%d_%s", A.prec, px ? "px" : "r"), name), s, bytes(A, px)) {}
+};
+
+// CG's scalar steps move into its vector kernels up to this many partials:
+// every workgroup then sums them (32 KB from L2).  At 16^3x32, 3 columns, FP16
+// (1024 partials) the four kernels of 18.4 us become two of 11.6 us; with the
+// 6912 of 24^3x64 the sums would read ten times the vectors.
+constexpr int kCgFold = 1024;
+
 namespace {
 struct Counters {
   int iters = 0, reliable = 0, restarts = 0;
@@ -233,24 +251,49 @@ int cg_mixed(Blas& bl, const Geom& g, const OpFn& A_hi, const OpFn& A_lo, int pl
   const bool defer = cnt.fault == 0;
   int skip = 0, since = 0;
   int it = 0;
+  const int gx = cg_grid(plo, nc, npar, g.Vh);
+  DBuf rpart(sizeof(double) * 4 * (size_t)gx * n, s);
+  if (!rpart.p) return fail(LQ_ENOMEM, "reduction partials");
+  auto cg_args = [&](const double* pin, int nin, bool fold) {
+    CgArgs A{};
+    A.prec = plo; A.nc = nc; A.ncol = na; A.npar = npar; A.Vh = g.Vh;
+    A.p = p.f; A.q = q.f; A.x = xs.f; A.r = rs.f;
+    A.st = st.d(); A.pin = pin; A.nin = nin; A.pout = rpart.as<double>(); A.gridx = gx; A.fold = fold;
+    return A;
+  };
+  // x += alpha p, p = r + beta p; fold: beta from the partials of |r|^2
+  auto step_px = [&](bool fold) -> int {
+    const CgArgs A = cg_args(rpart.as<double>(), gx, fold);
+    CgProf pr(bl.ctx, A, true, s);
+    return launch_cg_px(A, s) ? fail(LQ_EDEVICE, "cg vectors") : 0;
+  };
   for (; it < maxiter && na > 0; ++it) {
     Vec pv = view(p, 0, na), qv = view(q, 0, na), xsv = view(xs, 0, na), rsv = view(rs, 0, na);
+    const bool fold_a = A_fused && fused_tiles <= kCgFold;
     if (A_fused) {
       if ((e = (*A_fused)(qv, pv, 1, redbuf.as<double>()))) return e;
-      if (launch_scalar(SC_CG_ALPHA, redbuf.as<double>(), fused_tiles, na, st.d(), s))
+      if (!fold_a && launch_scalar(SC_CG_ALPHA, redbuf.as<double>(), fused_tiles, na, st.d(), s))
         return fail(LQ_EDEVICE, "scalar");
     } else {
       if ((e = A_lo(qv, pv))) return e;
       if ((e = bl.op(OP_DOT, &pv, &qv))) return e;
       if (launch_scalar(SC_CG_ALPHA, bl.partial, bl.gridx, na, st.d(), s)) return fail(LQ_EDEVICE, "scalar");
     }
-    if ((e = bl.op(OP_CG, &pv, &qv, &xsv, &rsv, nullptr, st.d(), ST_ALPHA, ST_ALPHA))) return e;
-    if (launch_scalar(SC_CG_BETA, bl.partial, bl.gridx, na, st.d(), s)) return fail(LQ_EDEVICE, "scalar");
+    {
+      const CgArgs A = cg_args(redbuf.as<double>(), fused_tiles, fold_a);
+      CgProf pr(bl.ctx, A, false, s);
+      if (launch_cg_r(A, s)) return fail(LQ_EDEVICE, "cg vectors");
+    }
     ++since;
-    if (defer && skip > 0 && it < maxiter - 1) {
+    // without a look at the state this iteration ends here
+    const bool blind = defer && skip > 0 && it < maxiter - 1;
+    const bool fold_b = blind && fused_tiles <= kCgFold;
+    if (!fold_b && launch_scalar(SC_CG_BETA, rpart.as<double>(), gx, na, st.d(), s))
+      return fail(LQ_EDEVICE, "scalar");
+    if (blind) {
       --skip;
       dirty = true;
-      if ((e = bl.op(OP_XPAY, &rsv, &pv, nullptr, nullptr, nullptr, st.d(), ST_BETA, ST_BETA))) return e;
+      if ((e = step_px(fold_b))) return e;
       continue;
     }
     if (cnt.fault == 1 && it == 0) {
@@ -282,7 +325,13 @@ int cg_mixed(Blas& bl, const Geom& g, const OpFn& A_hi, const OpFn& A_lo, int pl
     }
     for (int c = 0; c < na; ++c) rr_chk[c] = st.h(c, ST_RR);
     since = 0;
-    if (update && rule.converged_few() && it < maxiter - 1) {
+    if (!update && it < maxiter - 1) {
+      if ((e = step_px(false))) return e;
+      continue;
+    }
+    // x takes its step; p waits for what the update makes of r and beta
+    if ((e = bl.op(OP_AXPY, &pv, &xsv, nullptr, nullptr, nullptr, st.d(), ST_ALPHA, ST_ALPHA))) return e;
+    if (rule.converged_few() && update && it < maxiter - 1) {
       // Only a few columns are below their targets: fold every column's sloppy
       // updates into x, move those columns to slots [0, m) and recompute the
       // FP64 residual of these alone; the others keep iterating untouched.
@@ -315,7 +364,7 @@ int cg_mixed(Blas& bl, const Geom& g, const OpFn& A_hi, const OpFn& A_lo, int pl
         }
       }
       if ((e = compact())) return e;
-    } else if (update || it == maxiter - 1) {
+    } else {
       ++cnt.reliable;
       if ((e = launch_axpy_mixed(x.f, 64, xs.f, plo, nc, na, npar, g.Vh, s))) return fail(LQ_EDEVICE, "axpy");
       if ((e = vec_zero(xsv))) return e;
@@ -1402,9 +1451,16 @@ int solve(lq_ctx* c, const lq_action* act, lq_field* f, const lq_params* prm, in
         if (r) return r;
         return kind == LQ_OVERLAP ? overlap_D(env, plo, o, t, true) : wilson_D(env, plo, o, t, true);
       };
+      // <p, D^dag D p> = |D p|^2, from the epilogue of the first product
+      FusedFn Nfused = [&](Vec& o, const Vec& i, int, double* red) {
+        Vec t = view(tmplo, 0, i.ncol);
+        int r = wilson_D(env, plo, t, i, false, red);
+        return r ? r : wilson_D(env, plo, o, t, true);
+      };
       std::vector<double> tol_n(n_rhs, 0.1 * tol);
       for (int pass = 0; pass < 6; ++pass) {
-        const int rs = cg_mixed(bl, g, N64, Nlo, plo, x, bn, tol_n, maxiter, delta, cnt);
+        const int rs = cg_mixed(bl, g, N64, Nlo, plo, x, bn, tol_n, maxiter, delta, cnt, nullptr,
+                                kind == LQ_WILSON ? &Nfused : nullptr);
         if (rs != LQ_OK && rs != LQ_ENOCONV) return rs;
         if ((e = rel_residual(bl, D64, x, b, res, g))) return e;
         worst = *std::max_element(res.begin(), res.end());

@@ -6,6 +6,7 @@
 // reading psi on parity 1-p (the dagger swaps the two projectors), then one of
 //   EPI_HOP         out = k hop
 //   EPI_XPAY        out = a x + k hop                 (Wilson D)
+//   EPI_XPAY_NORM   the same and |out|^2              (CG on D^dag D: <p, D^dag D p> = |D p|^2)
 //   EPI_XPAY_G5     out = g5 (a x + k hop)            (H_W = g5 D_W(-rho), sec. 2.3)
 //   EPI_CLOVINV     out = A^{-1} (k hop)              (first half of the Schur operator)
 //   EPI_CLOVINV_XPAY out = A^{-1} (x + k hop)         (even-odd source, odd-site reconstruction)
@@ -232,7 +233,7 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(1, kStencilMaxThreads
 wilson_kernel(WilsonArgs A) {
   using R = typename RealOf<P>::T;
   constexpr bool XMY = EPI == EPI_XMY_CLOVINV || EPI == EPI_XMY_RTS;
-  constexpr bool RED = EPI == EPI_XMY_RTS;
+  constexpr bool RED = EPI == EPI_XMY_RTS || EPI == EPI_XPAY_NORM;
   if (A.ncol <= 0) return;
   const int ngrp = (A.ncol + NR - 1) / NR;
   int par, cb, grp, c[4], tile = 0;
@@ -310,13 +311,20 @@ wilson_kernel(WilsonArgs A) {
           }
         }
       }
-    } else if constexpr (EPI == EPI_XPAY || EPI == EPI_XPAY_G5 || EPI == EPI_CHEB) {
+    } else if constexpr (EPI == EPI_XPAY || EPI == EPI_XPAY_NORM || EPI == EPI_XPAY_G5 || EPI == EPI_CHEB) {
       cx<R> x[12];
       IO<P, 12>::template load<true>(A.x, blk_index(A.x, col, par), cb, x);
       const R a = A.acol ? (R)A.acol[col] : (R)A.a;
 #pragma unroll
       for (int i = 0; i < 12; ++i) out[i] = a * x[i] + acc[r][i];
-      if constexpr (EPI != EPI_XPAY) {
+      if constexpr (EPI == EPI_XPAY_NORM) {
+        if (live) {
+#pragma unroll
+          for (int i = 0; i < 12; ++i)
+            red[r][0] += (double)out[i].re * (double)out[i].re + (double)out[i].im * (double)out[i].im;
+        }
+      }
+      if constexpr (EPI == EPI_XPAY_G5 || EPI == EPI_CHEB) {
 #pragma unroll
         for (int i = 6; i < 12; ++i) out[i] = -out[i];
       }
@@ -380,7 +388,7 @@ inline void launch_one(const WilsonArgs& A, int bs, hipStream_t s) {
 // epilogues with register-blocked variants (NR > 1)
 constexpr bool epi_blocked(int epi) {
   return epi == EPI_CLOVINV || epi == EPI_XMY_CLOVINV || epi == EPI_XPAY || epi == EPI_XPAY_G5 || epi == EPI_CHEB ||
-         epi == EPI_XMY_RTS || epi == EPI_SITE || epi == EPI_CLOVINV_XPAY;
+         epi == EPI_XMY_RTS || epi == EPI_SITE || epi == EPI_CLOVINV_XPAY || epi == EPI_XPAY_NORM;
 }
 
 template <int P, int NE, int EPI>
@@ -415,6 +423,9 @@ inline int launch_epi(const WilsonArgs& A, int nr, int bs, hipStream_t s) {
   switch (A.epi) {
     case EPI_HOP: return launch_nr<P, NE, EPI_HOP>(A, nr, bs, s);
     case EPI_XPAY: return launch_nr<P, NE, EPI_XPAY>(A, nr, bs, s);
+    case EPI_XPAY_NORM:
+      if (A.dag) return -1;
+      return launch_nr<P, NE, EPI_XPAY_NORM>(A, nr, bs, s);
     case EPI_XPAY_G5: return launch_nr<P, NE, EPI_XPAY_G5>(A, nr, bs, s);
     case EPI_CHEB: return launch_nr<P, NE, EPI_CHEB>(A, nr, bs, s);
     default: break;
