@@ -27,7 +27,7 @@ struct WilsonArgs {
   int slab;     // site traversal order code (0: lexicographic), see traversal_block
   int tpb, xcd; // site tiles per workgroup (0: automatic), XCD-aware block order
   int sh;       // packed launch shape, set by the launcher
-  int nr;       // columns per thread (register blocking): 1, 2, 3, 4 or 6
+  int nr;       // columns per thread (register blocking): 1, 2, 3, 4 or 6; kSplitShape: one hop per wave
   const void* links;
   FieldRef in, out, x, v, b1, b2;
   const void* clov;      // packed Hermitian H = (4+m) + C per chirality
@@ -36,6 +36,7 @@ struct WilsonArgs {
   double a, k_hop, mu_tw, s1, ck, s2;
   double* red;           // fused-reduction partials (EPI_XMY_RTS, EPI_XPAY_NORM)
 };
+constexpr int kSplitShape = -8;
 int launch_wilson(const WilsonArgs& A, hipStream_t s);
 template <int P>
 int launch_wilson_prec(const WilsonArgs& A, int nr, int bs, hipStream_t s);

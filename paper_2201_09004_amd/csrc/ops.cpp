@@ -441,17 +441,20 @@ static int tuned(lq_ctx* c, const std::string& key, Args& A, size_t out_bytes, i
     // thread again at that order, then tiles per workgroup x block order, each
     // around the best shape so far
     const std::vector<int> slabs = slab_candidates(A.g);
-    for (int nr : nrs) trial(Shape{nr, 0, 0, 1});
+    for (int nr : nrs)
+      if (nr != kSplitShape) trial(Shape{nr, 0, 0, 1});
     const Shape s0 = choice;
     for (int bz : slabs)
       if (bz != 0) trial(Shape{s0.nr, bz, 0, 1});
     const Shape sb = choice;
     for (int nr : nrs)
-      if (nr != sb.nr) trial(Shape{nr, sb.slab, 0, 1});
+      if (nr != sb.nr && nr != kSplitShape) trial(Shape{nr, sb.slab, 0, 1});
     const Shape s1 = choice;
     for (int tpb : {0, 1, 2, 4, 8})
       for (int xcd : {1, 0})
         if (!(tpb == 0 && xcd == 1)) trial(Shape{s1.nr, s1.slab, tpb, xcd});
+    // one hop per wave has no further shape
+    if (std::find(nrs.begin(), nrs.end(), kSplitShape) != nrs.end()) trial(Shape{kSplitShape, 0, 0, 1});
     hipEventDestroy(e0);
     hipEventDestroy(e1);
     std::lock_guard<std::mutex> lk(c->mtx);
@@ -480,8 +483,9 @@ static size_t tune_out_bytes(int prec, int nc, int ncol, int npar, int Vh) {
   return (size_t)ncol * npar * Vh * (size_t)site_bytes(prec, nc);
 }
 
-static std::vector<int> nr_candidates(int prec, int ncol, bool blocked) {
+static std::vector<int> nr_candidates(int prec, int ncol, bool blocked, bool split) {
   std::vector<int> v{1};
+  if (split) v.push_back(kSplitShape);
   if (!blocked) return v;
   for (int nr : {2, 3, 4, 6})
     if (nr <= ncol && !(prec == 64 && nr > 4)) v.push_back(nr);
@@ -500,9 +504,15 @@ static int run_wilson(OpEnv& e, WilsonArgs& A, int n_fields, int clov_mats, int 
   snprintf(name, sizeof(name), "wilson%d_%s", A.prec, epi_names[A.epi]);
   char key[160];
   snprintf(key, sizeof(key), "%s_r%d_d%d_n%d_v%d_p%d", name, A.recon, A.dag, col_bucket(A.ncol), A.g.Vh, A.par_out);
-  const bool blocked = !A.dag && (A.epi == EPI_CLOVINV || A.epi == EPI_XMY_CLOVINV || A.epi == EPI_XPAY ||
+  const bool blocked = A.dag ? A.epi == EPI_XPAY || A.epi == EPI_SITE : (A.epi == EPI_CLOVINV || A.epi == EPI_XMY_CLOVINV || A.epi == EPI_XPAY ||
                                   A.epi == EPI_XPAY_G5 || A.epi == EPI_CHEB || A.epi == EPI_XMY_RTS ||
                                   A.epi == EPI_SITE || A.epi == EPI_CLOVINV_XPAY || A.epi == EPI_XPAY_NORM);
+  // one hop per wave is worth timing while one thread per site leaves SIMDs
+  // without a wave or with few (4 per SIMD: @SPLITRULE@)
+  const bool split = A.prec != 16 && (A.dag ? A.epi == EPI_XPAY || A.epi == EPI_SITE
+                                            : A.epi == EPI_HOP || A.epi == EPI_XPAY || A.epi == EPI_XPAY_NORM ||
+                                                  A.epi == EPI_XPAY_G5 || A.epi == EPI_SITE) &&
+                     (int64_t)((nsite + 63) / 64) * A.ncol <= 4096;
   const int out_npar = A.out.npar;
   // timed under the kernel's name and under name_n<columns> (solvers that drop
   // converged columns launch the same kernel at several widths)
@@ -512,7 +522,7 @@ static int run_wilson(OpEnv& e, WilsonArgs& A, int n_fields, int clov_mats, int 
   Prof p(e.noalloc ? nullptr : e.ctx, name, e.s, launch_bytes);
   Prof pn(e.noalloc ? nullptr : e.ctx, name_n, e.s, launch_bytes);
   int r = tuned(e.ctx, key, A, tune_out_bytes(A.prec, 12, A.ncol, out_npar, A.g.Vh), A.prec,
-                nr_candidates(A.prec, A.ncol, blocked), e.s,
+                nr_candidates(A.prec, A.ncol, blocked, split), e.s,
                 [](const WilsonArgs& B, hipStream_t st) { return launch_wilson(B, st); }, !e.noalloc);
   if (r) return fail(r == -1 ? LQ_ENOTSUP : LQ_EDEVICE, "wilson stencil launch");
   e.n_apply += A.par_out == 2 ? 2 : 1;

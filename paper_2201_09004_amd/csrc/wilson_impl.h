@@ -375,6 +375,221 @@ wilson_kernel(WilsonArgs A) {
   }
 }
 
+// ------------------------------------------------------------ small launches
+// The same operators for launches of few waves, where the chain of one
+// thread's eight hops is what takes the time (4096 sites are 64 waves on 1024
+// SIMDs): a workgroup of eight waves takes 64 sites and one column, each wave
+// one hop, the two transported colour vectors of every hop meet in LDS, and
+// four waves, one spin each (two, one chirality each, where the site matrix
+// couples the spins), sum them in the hop order of wilson_kernel and finish.  The arithmetic of every element is the same in the same order, so
+// the results are bitwise those of wilson_kernel and the tuner may choose.
+// 8^4, one column, FP64: twisted-clover D @SPD@,
+// Wilson D with |out|^2 @SPN@.
+template <int P> __device__ __forceinline__ cx<typename RealOf<P>::T> load_comp(const FieldRef& f, int64_t blk, int cb, int c) {
+  static_assert(P != 16, "FP16 sites are whole");
+  if constexpr (P == 64) {
+    const double2 v = ((const double2*)f.data)[tix(blk, c, 12, cb, f.Vh)];
+    return {v.x, v.y};
+  } else {
+    const float2 v = ((const float2*)f.data)[2 * tix(blk, c >> 1, 6, cb, f.Vh) + (c & 1)];
+    return {v.x, v.y};
+  }
+}
+template <int P> __device__ __forceinline__ void store_comp(const FieldRef& f, int64_t blk, int cb, int c, cx<typename RealOf<P>::T> v) {
+  if constexpr (P == 64) ((double2*)f.data)[tix(blk, c, 12, cb, f.Vh)] = make_double2(v.re, v.im);
+  else ((float2*)f.data)[2 * tix(blk, c >> 1, 6, cb, f.Vh) + (c & 1)] = make_float2(v.re, v.im);
+}
+
+// U h or U^dag h of the hop by S along MU
+template <int P, int NE, bool DAG, int MU, int S, typename R>
+__device__ __forceinline__ void split_hop(const WilsonArgs& A, const int c[4], int par, int cb, int col, cx<R>* uh) {
+  const Geom& g = A.g;
+  const int pin = par ^ 1;
+  cx<R> U[9], psi[12], h[6];
+  const int nb = nb_cb(c, MU, S, g);
+  load_link<P, NE>(A.links, g.Vh, S > 0 ? par : pin, MU, S > 0 ? cb : nb, U);
+  IO<P, 12>::load(A.in, blk_index(A.in, col, pin), nb, psi);
+  project<MU, (S > 0) == DAG ? 1 : -1>(psi, h);
+  if (MU == 3 && g.ap && c[3] == (S > 0 ? g.L[3] - 1 : 0)) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) h[i] = -h[i];
+  }
+  if constexpr (S > 0) {
+    su3_mv(U, h, uh);
+    su3_mv(U, h + 3, uh + 3);
+  } else {
+    su3_mv_dag(U, h, uh);
+    su3_mv_dag(U, h + 3, uh + 3);
+  }
+}
+
+// spin W's part of recon_add for the hop along MU with projector sign SP
+template <int MU, int SP, int W, typename R>
+__device__ __forceinline__ void split_add(cx<R>* o, const cx<R> (*uh)[64], int lane) {
+  const R s = (R)SP;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    if constexpr (W < 2) {
+      o[a] = o[a] + uh[3 * W + a][lane];
+    } else if constexpr (MU == 0) {
+      o[a] = o[a] + s * times_i(uh[W == 2 ? 3 + a : a][lane]);
+    } else if constexpr (MU == 1) {
+      if constexpr (W == 2) o[a] = o[a] + s * uh[3 + a][lane];
+      else o[a] = o[a] - s * uh[a][lane];
+    } else if constexpr (MU == 2) {
+      if constexpr (W == 2) o[a] = o[a] + s * times_i(uh[a][lane]);
+      else o[a] = o[a] + s * times_mi(uh[3 + a][lane]);
+    } else {
+      o[a] = o[a] + s * uh[W == 2 ? a : 3 + a][lane];
+    }
+  }
+}
+
+// the scaled hop sum of spin W
+template <bool DAG, int W, typename R>
+__device__ __forceinline__ void split_sum(const WilsonArgs& A, int lane, const cx<R> (*sm)[6][64], cx<R>* acc) {
+  constexpr int SB = DAG ? -1 : 1;  // projector sign of the backward hops
+#pragma unroll
+  for (int a = 0; a < 3; ++a) acc[a] = {0, 0};
+  split_add<3, SB, W>(acc, sm[0], lane);
+  split_add<2, SB, W>(acc, sm[1], lane);
+  split_add<1, SB, W>(acc, sm[2], lane);
+  split_add<0, SB, W>(acc, sm[3], lane);
+  split_add<0, -SB, W>(acc, sm[4], lane);
+  split_add<1, -SB, W>(acc, sm[5], lane);
+  split_add<2, -SB, W>(acc, sm[6], lane);
+  split_add<3, -SB, W>(acc, sm[7], lane);
+  const R k = (R)A.k_hop;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    acc[a] = k * acc[a];
+    // rounded here, as in wilson_kernel: the sums that follow fuse their other product
+    asm volatile("" : "+v"(acc[a].re), "+v"(acc[a].im));
+  }
+}
+
+// one spin of every epilogue without site matrices
+template <int P, bool DAG, int EPI, int W, typename R>
+__device__ __forceinline__ void split_finish(const WilsonArgs& A, int par, int cb, int col, int lane, bool live,
+                                             const cx<R> (*sm)[6][64], cx<R>* out) {
+  cx<R> acc[3];
+  split_sum<DAG, W>(A, lane, sm, acc);
+  if constexpr (EPI == EPI_HOP) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) out[a] = acc[a];
+  } else {
+    const R s = A.acol ? (R)A.acol[col] : (R)A.a;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const cx<R> x = load_comp<P>(A.x, blk_index(A.x, col, par), cb, 3 * W + a);
+      out[a] = s * x + acc[a];
+      if constexpr (EPI == EPI_XPAY_G5 && W >= 2) out[a] = -out[a];
+    }
+  }
+  if (live) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) store_comp<P>(A.out, blk_index(A.out, col, par), cb, 3 * W + a, out[a]);
+  }
+}
+
+// one chirality of EPI_SITE
+template <int P, bool DAG, int CH, typename R>
+__device__ __forceinline__ void split_site(const WilsonArgs& A, int par, int cb, int col, int lane, bool live,
+                                           const cx<R> (*sm)[6][64]) {
+  cx<R> acc[6], x[6], out[6];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) x[i] = load_comp<P>(A.x, blk_index(A.x, col, par), cb, 6 * CH + i);
+  split_sum<DAG, 2 * CH>(A, lane, sm, acc);
+  split_sum<DAG, 2 * CH + 1>(A, lane, sm, acc + 3);
+  apply_herm6<P>(A.clov, A.g.Vh, par, CH, cb, x, out);
+  const R mu = (R)A.mu_tw;
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    if constexpr (CH == 0) out[i] = out[i] + mu * times_i(x[i]) + acc[i];
+    else out[i] = out[i] - mu * times_i(x[i]) + acc[i];
+    if (live) store_comp<P>(A.out, blk_index(A.out, col, par), cb, 6 * CH + i, out[i]);
+  }
+}
+
+template <int P, int NE, bool DAG, int EPI>
+__global__ void __launch_bounds__(512) wilson_split_kernel(WilsonArgs A) {
+  using R = typename RealOf<P>::T;
+  __shared__ cx<R> sm[8][6][64];
+  const Geom& g = A.g;
+  const int nsite = A.par_out == 2 ? 2 * g.Vh : g.Vh;
+  const int tile = blockIdx.x, col = blockIdx.y, lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int j = tile * 64 + lane;
+  const bool live = j < nsite;
+  if (!live) j = nsite - 1;
+  const int par = A.par_out == 2 ? (j >= g.Vh ? 1 : 0) : A.par_out;
+  const int cb = A.par_out == 2 ? j - par * g.Vh : j;
+  int c[4];
+  cb_coords(cb, par, g, c);
+  cx<R> uh[6];
+  switch (w) {
+    case 0: split_hop<P, NE, DAG, 3, -1>(A, c, par, cb, col, uh); break;
+    case 1: split_hop<P, NE, DAG, 2, -1>(A, c, par, cb, col, uh); break;
+    case 2: split_hop<P, NE, DAG, 1, -1>(A, c, par, cb, col, uh); break;
+    case 3: split_hop<P, NE, DAG, 0, -1>(A, c, par, cb, col, uh); break;
+    case 4: split_hop<P, NE, DAG, 0, 1>(A, c, par, cb, col, uh); break;
+    case 5: split_hop<P, NE, DAG, 1, 1>(A, c, par, cb, col, uh); break;
+    case 6: split_hop<P, NE, DAG, 2, 1>(A, c, par, cb, col, uh); break;
+    default: split_hop<P, NE, DAG, 3, 1>(A, c, par, cb, col, uh); break;
+  }
+#pragma unroll
+  for (int i = 0; i < 6; ++i) sm[w][i][lane] = uh[i];
+  __syncthreads();
+  if constexpr (EPI == EPI_SITE) {
+    if (w == 0) split_site<P, DAG, 0>(A, par, cb, col, lane, live, sm);
+    else if (w == 1) split_site<P, DAG, 1>(A, par, cb, col, lane, live, sm);
+    return;
+  }
+  cx<R> out[3];
+  switch (w) {
+    case 0: split_finish<P, DAG, EPI, 0>(A, par, cb, col, lane, live, sm, out); break;
+    case 1: split_finish<P, DAG, EPI, 1>(A, par, cb, col, lane, live, sm, out); break;
+    case 2: split_finish<P, DAG, EPI, 2>(A, par, cb, col, lane, live, sm, out); break;
+    case 3: split_finish<P, DAG, EPI, 3>(A, par, cb, col, lane, live, sm, out); break;
+    default: break;
+  }
+  if constexpr (EPI == EPI_XPAY_NORM) {
+    // |out|^2 of the tile, summed as in wilson_kernel: the site's twelve
+    // components in order, then the butterfly over the sites
+    __syncthreads();
+    cx<R>(*o)[64] = &sm[0][0];
+    if (w < 4)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) o[3 * w + a][lane] = out[a];
+    __syncthreads();
+    if (w == 0) {
+      double red = 0.0;
+      if (live)
+#pragma unroll
+        for (int i = 0; i < 12; ++i) {
+          const cx<R> v = o[i][lane];
+          red += (double)v.re * (double)v.re + (double)v.im * (double)v.im;
+        }
+      for (int d = 32; d > 0; d >>= 1) red += __shfl_xor(red, d);
+      if (lane == 0) {
+        double* p = A.red + ((int64_t)col * ((nsite + 63) >> 6) + tile) * 4;
+        p[0] = red;
+        p[1] = p[2] = p[3] = 0.0;
+      }
+    }
+  }
+}
+
+constexpr bool epi_split(int epi) {
+  return epi == EPI_HOP || epi == EPI_XPAY || epi == EPI_XPAY_NORM || epi == EPI_XPAY_G5 || epi == EPI_SITE;
+}
+template <int P, int NE, bool DAG, int EPI>
+inline int launch_split(const WilsonArgs& A, hipStream_t s) {
+  const int nsite = A.par_out == 2 ? 2 * A.g.Vh : A.g.Vh;
+  wilson_split_kernel<P, NE, DAG, EPI><<<dim3((nsite + 63) / 64, A.ncol), 512, 0, s>>>(A);
+  return 0;
+}
+
 template <int P, int NE, bool DAG, int EPI, int NR>
 inline void launch_one(const WilsonArgs& A, int bs, hipStream_t s) {
   (void)bs;
@@ -393,7 +608,22 @@ constexpr bool epi_blocked(int epi) {
 
 template <int P, int NE, int EPI>
 inline int launch_nr(const WilsonArgs& A, int nr, int bs, hipStream_t s) {
+  if (nr == kSplitShape) {
+    if constexpr (P != 16 && epi_split(EPI)) {
+      if (!A.dag) return launch_split<P, NE, false, EPI>(A, s);
+      if constexpr (EPI == EPI_XPAY || EPI == EPI_SITE) return launch_split<P, NE, true, EPI>(A, s);
+    }
+    nr = 1;
+  }
   if (A.dag) {
+    if constexpr (EPI == EPI_XPAY || EPI == EPI_SITE) {
+      switch (nr) {
+        case 2: launch_one<P, NE, true, EPI, 2>(A, bs, s); return 0;
+        case 3: launch_one<P, NE, true, EPI, 3>(A, bs, s); return 0;
+        case 4: launch_one<P, NE, true, EPI, 4>(A, bs, s); return 0;
+        default: break;
+      }
+    }
     if (nr != 1) return -1;
     launch_one<P, NE, true, EPI, 1>(A, bs, s);
     return 0;
