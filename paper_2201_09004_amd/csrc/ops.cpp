@@ -508,7 +508,10 @@ static int run_wilson(OpEnv& e, WilsonArgs& A, int n_fields, int clov_mats, int 
                                   A.epi == EPI_XPAY_G5 || A.epi == EPI_CHEB || A.epi == EPI_XMY_RTS ||
                                   A.epi == EPI_SITE || A.epi == EPI_CLOVINV_XPAY || A.epi == EPI_XPAY_NORM);
   // one hop per wave is worth timing while one thread per site leaves SIMDs
-  // without a wave or with few (4 per SIMD: @SPLITRULE@)
+  // without a wave or with few (at most 4 per SIMD).  Between events, one thread
+  // per site against one hop per wave, FP64 twisted-clover D: 64 waves 27 and 19
+  // us, 384 waves 33 and 22, 648 waves 36 and 35, 972 waves 38 and 42, 3072
+  // waves of one column 107 and 97, of three columns 67 and 88
   const bool split = A.prec != 16 && (A.dag ? A.epi == EPI_XPAY || A.epi == EPI_SITE
                                             : A.epi == EPI_HOP || A.epi == EPI_XPAY || A.epi == EPI_XPAY_NORM ||
                                                   A.epi == EPI_XPAY_G5 || A.epi == EPI_SITE) &&
