@@ -55,7 +55,7 @@ __device__ __forceinline__ double norm_acc(const cx<R>* a) {
 
 constexpr bool op_reduces(int op) {
   return op == OP_CG || op == OP_BICG_XR || op == OP_DOT || op == OP_NORM2 || op == OP_DOT_NORM ||
-         op == OP_XMY_NORM;
+         op == OP_XMY_NORM || op == OP_GCR_R;
 }
 
 template <int P, int NC, int OP>
@@ -144,6 +144,13 @@ __global__ void __launch_bounds__(256) blas_kernel(BlasArgs A) {
       for (int k = 0; k < NC; ++k) b[k] = a[k] - b[k];
       IOt::store(A.f[1], blk, cb, b);
       red[0] += norm_acc<R, NC>(b);
+    } else if constexpr (OP == OP_GCR_R) {
+      IOt::load(A.f[0], blk, cb, a);
+      IOt::load(A.f[1], blk, cb, b);
+#pragma unroll
+      for (int k = 0; k < NC; ++k) b[k] = b[k] - c0 * a[k];
+      IOt::store(A.f[1], blk, cb, b);
+      red[0] += norm_acc<R, NC>(b);
     } else if constexpr (OP == OP_ZERO) {
 #pragma unroll
       for (int k = 0; k < NC; ++k) a[k] = {0, 0};
@@ -197,7 +204,7 @@ static void blas_dispatch(const BlasArgs& A, dim3 grid, dim3 block, hipStream_t 
   switch (A.op) {
     LQ_OPC(OP_AXPY) LQ_OPC(OP_AXMY) LQ_OPC(OP_XPAY) LQ_OPC(OP_CG) LQ_OPC(OP_BICG_XR) LQ_OPC(OP_BICG_P)
     LQ_OPC(OP_DOT) LQ_OPC(OP_NORM2) LQ_OPC(OP_DOT_NORM) LQ_OPC(OP_XMY_NORM) LQ_OPC(OP_ZERO) LQ_OPC(OP_SCALE)
-    LQ_OPC(OP_G5) LQ_OPC(OP_LC_G5) LQ_OPC(OP_COPY) LQ_OPC(OP_PLC)
+    LQ_OPC(OP_G5) LQ_OPC(OP_LC_G5) LQ_OPC(OP_COPY) LQ_OPC(OP_GCR_R) LQ_OPC(OP_PLC)
     default: break;
   }
 #undef LQ_OPC
@@ -352,6 +359,25 @@ __global__ void scalar_kernel(int op, const double* partial, int gridx, int ncol
 int launch_scalar(int op, const double* partial, int gridx, int ncol, double* st, hipStream_t s) {
   if (ncol == 0) return 0;
   scalar_kernel<<<ncol, kScalarThreads, 0, s>>>(op, partial, gridx, ncol, st);
+  return hipGetLastError() == hipSuccess ? 0 : -3;
+}
+
+__global__ void scalar_gcr_kernel(const double* partial, int gridx, double* st, double* alpha, double* iw2) {
+  const int col = blockIdx.x;
+  double* s = st + (int64_t)col * ST_STRIDE;
+  const double* p = partial + (int64_t)col * gridx * 4;
+  const double re = sum_r(p, gridx, 0), im = sum_r(p, gridx, 1), ww = sum_r(p, gridx, 2);
+  if (threadIdx.x > 0) return;
+  const double inv = ww > 0.0 ? 1.0 / ww : 0.0;
+  if (!isfinite(inv) || !isfinite(re) || !isfinite(im)) s[ST_FLAG] = 2;
+  s[ST_ALPHA] = alpha[2 * col] = re * inv;
+  s[ST_ALPHA + 1] = alpha[2 * col + 1] = im * inv;
+  iw2[col] = inv;
+}
+int launch_scalar_gcr(const double* partial, int gridx, int ncol, double* st, double* alpha, double* iw2,
+                      hipStream_t s) {
+  if (ncol == 0) return 0;
+  scalar_gcr_kernel<<<ncol, kScalarThreads, 0, s>>>(partial, gridx, st, alpha, iw2);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 

@@ -310,9 +310,16 @@ bool mg_matches(const MgHier* h, const lq_action* act);
 // the setup's probe vectors on the fine lattice (FP64, ncol <= 12 columns): basis vector
 // (k0 + kk) of the aggregates of coarse parity class cls in column kk, zero elsewhere (mg.hip)
 int launch_mg_probe_fine(const MgGeom& m, const void* Q64, FieldRef fine, int ncol, int k0, int cls, hipStream_t s);
-// one classical Gram-Schmidt step over k <= 8 directions (mg.hip): coef[j][col] = <W_j, w>,
-// then w -= sum_j coef_j W_j and z -= sum_j coef_j Z_j; partial holds k * ncol * gridx * 2 doubles
-int launch_mg_cgs(int prec, const FieldRef* W, const FieldRef* Z, int k, FieldRef w, FieldRef z, int ncol, int npar,
-                  int gridx, double* partial, double* coef, hipStream_t s);
+// vector kernels of the outer flexible GCR over k <= 8 directions (mg.hip).  dots: coef[j][col] =
+// <W_j, w> iw2[j][col], partial k * ncol * gridx * 2 doubles; orth: w -= sum_j coef_j W_j and, with red
+// ([ncol][gridx][4]), <w, r> and |w|^2; solve: the cycle's coefficients y from alpha[k][col] and
+// c[l][k][col] (rows of kmax); update: x (FP64) += sum_j y_j Z_j
+int launch_mg_gcr_dots(int prec, const FieldRef* W, int k, FieldRef w, int ncol, int npar, int gridx, double* partial,
+                       const double* iw2, double* coef, hipStream_t s);
+int launch_mg_gcr_orth(int prec, const FieldRef* W, int k, FieldRef w, FieldRef r, int ncol, int npar, int gridx,
+                       const double* coef, double* red, hipStream_t s);
+int launch_mg_gcr_solve(const double* alpha, const double* c, int n, int kmax, int ncol, double* y, hipStream_t s);
+int launch_mg_gcr_update(int prec, const FieldRef* Z, int k, FieldRef x, int ncol, int npar, int gridx,
+                         const double* y, hipStream_t s);
 
 }  // namespace lq

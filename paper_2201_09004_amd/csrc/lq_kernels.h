@@ -103,6 +103,7 @@ enum {
   OP_G5,         // f1 = g5 f0 (Wilson only)
   OP_LC_G5,      // f2 = c0 f0 + c1 g5 f1 (Wilson only)
   OP_COPY,       // f1 = f0
+  OP_GCR_R,      // f1 -= c0 f0 ; red |f1|^2
   OP_PLC,        // f2 = p0 f0 + p1 (p2 f1 + p3 g5 f1), real p0..p3 per column from pcol (Wilson only)
   OP_NCOUNT
 };
@@ -150,6 +151,9 @@ int launch_axpy_mixed(FieldRef y, int py, FieldRef x, int px, int nc, int ncol, 
 enum { SC_CG_ALPHA = 0, SC_CG_BETA, SC_BICG_ALPHA, SC_BICG_OMEGA, SC_BICG_BETA, SC_SET_RR, SC_SET_RHO_RR,
        SC_DOT_TO_AUX };
 int launch_scalar(int op, const double* partial, int gridx, int ncol, double* st, hipStream_t s);
+// GCR: alpha = <w, r> / |w|^2 to the state (ST_ALPHA) and alpha[col]; 1 / |w|^2 (0 for w = 0) to iw2[col]
+int launch_scalar_gcr(const double* partial, int gridx, int ncol, double* st, double* alpha, double* iw2,
+                      hipStream_t s);
 
 // multi-shift CG (Jegerlehner): fields with ncol = nshift * nrhs, shift-major.
 // x_i and p_i are updated from the residuals of up to kMsSlots iterations at

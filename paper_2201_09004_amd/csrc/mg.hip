@@ -455,10 +455,14 @@ __global__ void __launch_bounds__(256) mg_stencil_mfma_kernel(MgGeom m, const vo
 }
 
 // ---------------------------------------------------------------- block Gram-Schmidt
-// Classical Gram-Schmidt step of the outer flexible GCR on k <= 8 earlier
-// directions: c_j = <W_j, w> for all j in one pass over w (per-block partials,
-// summed in block order: deterministic), then w -= sum_j c_j W_j and
-// z -= sum_j c_j Z_j in one pass.
+// Vector kernels of the outer flexible GCR, up to 8 directions per pass over
+// the column.  The directions w_j = M z_j - sum_{i<j} c_ij w_i are orthogonal
+// but not scaled (1 / |w_j|^2 enters the coefficients), and the z_j stay as the
+// preconditioner made them: the combination that corrects x follows from the
+// c_ij when the cycle closes.  A step with k earlier directions takes 2k + 7
+// passes over a column (c_j: k + 1, orthogonalising with <w, r> and |w|^2: k +
+// 3, r and |r|^2: 3), where scaling, orthogonalising z alike and separate dot,
+// norm and axpy passes took 3k + 19.  All sums in block order: deterministic.
 struct MgVecSet {
   FieldRef f[8];
 };
@@ -506,48 +510,118 @@ __global__ void __launch_bounds__(256) mg_mdot_kernel(MgVecSet W, int k, FieldRe
   }
 }
 
-__global__ void mg_mdot_sum_kernel(const double* partial, int k, int ncol, int gridx, double* coef) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= k * ncol) return;
+// coef[j][col] = <w_j, w> / |w_j|^2, one wave per (j, col)
+__global__ void __launch_bounds__(64) mg_mdot_sum_kernel(const double* partial, const double* iw2, int gridx,
+                                                         double* coef) {
+  const int t = blockIdx.x;  // j * ncol + col
   const double* p = partial + (int64_t)t * gridx * 2;
   double re = 0.0, im = 0.0;
-  for (int b = 0; b < gridx; ++b) {
+  for (int b = threadIdx.x; b < gridx; b += 64) {
     re += p[2 * b];
     im += p[2 * b + 1];
   }
-  coef[2 * t] = re;
-  coef[2 * t + 1] = im;
+  for (int o = 32; o > 0; o >>= 1) {
+    re += __shfl_xor(re, o);
+    im += __shfl_xor(im, o);
+  }
+  if (threadIdx.x == 0) {
+    coef[2 * t] = re * iw2[t];
+    coef[2 * t + 1] = im * iw2[t];
+  }
 }
 
+// w -= sum_j c_j W_j, and with `partial` <w, r>, |w|^2 of the result
+// ([col][gridx][4], as the vector kernels of the solvers)
 template <int P>
-__global__ void __launch_bounds__(256) mg_maxmy_kernel(MgVecSet W, MgVecSet Z, int k, FieldRef w, FieldRef z,
-                                                        int npar, const double* coef) {
+__global__ void __launch_bounds__(256) mg_maxmy_kernel(MgVecSet W, int k, FieldRef w, FieldRef r, int npar,
+                                                        const double* coef, double* partial) {
   using R = typename CxT<P>::R;
+  __shared__ double sm[4][3];
   const int col = blockIdx.y, ncol = gridDim.y;
   const int64_t n = (int64_t)npar * w.Vh;
   cx<R> c[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j)
     c[j] = j < k ? cx<R>{(R)coef[2 * (j * ncol + col)], (R)coef[2 * (j * ncol + col) + 1]} : cx<R>{0, 0};
+  double red[3] = {0.0, 0.0, 0.0};
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const int par = (int)(i / w.Vh), cb = (int)(i - (int64_t)par * w.Vh);
     const int64_t blk = (int64_t)col * npar + par;
-    cx<R> x[12], y[12], a[12];
+    cx<R> x[12], a[12];
     IO<P, 12>::load(w, blk, cb, x);
-    IO<P, 12>::load(z, blk, cb, y);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       if (j < k) {
         IO<P, 12>::load(W.f[j], blk, cb, a);
 #pragma unroll
         for (int q = 0; q < 12; ++q) x[q] = x[q] - c[j] * a[q];
-        IO<P, 12>::load(Z.f[j], blk, cb, a);
-#pragma unroll
-        for (int q = 0; q < 12; ++q) y[q] = y[q] - c[j] * a[q];
       }
     }
     IO<P, 12>::store(w, blk, cb, x);
-    IO<P, 12>::store(z, blk, cb, y);
+    if (partial) {
+      IO<P, 12>::load(r, blk, cb, a);
+#pragma unroll
+      for (int q = 0; q < 12; ++q) {
+        red[0] += (double)x[q].re * (double)a[q].re + (double)x[q].im * (double)a[q].im;
+        red[1] += (double)x[q].re * (double)a[q].im - (double)x[q].im * (double)a[q].re;
+        red[2] += (double)x[q].re * (double)x[q].re + (double)x[q].im * (double)x[q].im;
+      }
+    }
+  }
+  if (!partial) return;
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+    for (int o = 32; o > 0; o >>= 1) red[j] += __shfl_xor(red[j], o);
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) sm[threadIdx.x >> 6][j] = red[j];
+  __syncthreads();
+  if (threadIdx.x < 3) {
+    double v = 0.0;
+    for (int q = 0; q < 4; ++q) v += sm[q][threadIdx.x];
+    partial[((int64_t)col * gridDim.x + blockIdx.x) * 4 + threadIdx.x] = v;
+  }
+}
+
+// y_k of x += sum_k y_k z_k from alpha_k and the unit upper triangle c[l][k] =
+// <w_k, M z_l> / |w_k|^2, k < l < n: y_k = alpha_k - sum_{l>k} c[l][k] y_l
+__global__ void mg_gcr_solve_kernel(const double* alpha, const double* c, int n, int kmax, int ncol, double* y) {
+  const int col = blockIdx.x * blockDim.x + threadIdx.x;
+  if (col >= ncol) return;
+  for (int k = n - 1; k >= 0; --k) {
+    double re = alpha[2 * (k * ncol + col)], im = alpha[2 * (k * ncol + col) + 1];
+    for (int l = k + 1; l < n; ++l) {
+      const double* q = c + 2 * (((int64_t)l * kmax + k) * ncol + col);
+      const double yr = y[2 * (l * ncol + col)], yi = y[2 * (l * ncol + col) + 1];
+      re -= q[0] * yr - q[1] * yi;
+      im -= q[0] * yi + q[1] * yr;
+    }
+    y[2 * (k * ncol + col)] = re;
+    y[2 * (k * ncol + col) + 1] = im;
+  }
+}
+
+// x (FP64) += sum_j y_j Z_j, summed in FP64
+template <int P>
+__global__ void __launch_bounds__(256) mg_xupdate_kernel(MgVecSet Z, int k, FieldRef x, int npar, const double* y) {
+  const int col = blockIdx.y, ncol = gridDim.y;
+  const int64_t n = (int64_t)npar * x.Vh;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    const int par = (int)(i / x.Vh), cb = (int)(i - (int64_t)par * x.Vh);
+    const int64_t blk = (int64_t)col * npar + par;
+    cx<double> v[12];
+    IO<64, 12>::load(x, blk, cb, v);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (j < k) {
+        const cx<double> c = {y[2 * (j * ncol + col)], y[2 * (j * ncol + col) + 1]};
+        cx<typename CxT<P>::R> a[12];
+        IO<P, 12>::load(Z.f[j], blk, cb, a);
+#pragma unroll
+        for (int q = 0; q < 12; ++q) fma(v[q], c, cx<double>{(double)a[q].re, (double)a[q].im});
+      }
+    }
+    IO<64, 12>::store(x, blk, cb, v);
   }
 }
 
@@ -965,21 +1039,45 @@ int launch_mg_random(FieldRef fine, int ncol, uint64_t seed, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 
-int launch_mg_cgs(int prec, const FieldRef* W, const FieldRef* Z, int k, FieldRef w, FieldRef z, int ncol, int npar,
-                  int gridx, double* partial, double* coef, hipStream_t s) {
-  if (k <= 0 || ncol <= 0) return 0;
-  if (k > 8 || (prec != 32 && prec != 64)) return -1;
-  MgVecSet Ws{}, Zs{};
-  for (int j = 0; j < k; ++j) {
-    Ws.f[j] = W[j];
-    Zs.f[j] = Z[j];
-  }
-  dim3 grid(gridx, ncol);
-  if (prec == 32) mg_mdot_kernel<32><<<grid, 256, 0, s>>>(Ws, k, w, npar, partial);
-  else mg_mdot_kernel<64><<<grid, 256, 0, s>>>(Ws, k, w, npar, partial);
-  mg_mdot_sum_kernel<<<(k * ncol + 63) / 64, 64, 0, s>>>(partial, k, ncol, gridx, coef);
-  if (prec == 32) mg_maxmy_kernel<32><<<grid, 256, 0, s>>>(Ws, Zs, k, w, z, npar, coef);
-  else mg_maxmy_kernel<64><<<grid, 256, 0, s>>>(Ws, Zs, k, w, z, npar, coef);
+static bool vec_set(MgVecSet& S, const FieldRef* V, int k, int ncol, int prec) {
+  if (k <= 0 || k > 8 || ncol <= 0 || (prec != 32 && prec != 64)) return false;
+  for (int j = 0; j < k; ++j) S.f[j] = V[j];
+  return true;
+}
+
+int launch_mg_gcr_dots(int prec, const FieldRef* W, int k, FieldRef w, int ncol, int npar, int gridx, double* partial,
+                       const double* iw2, double* coef, hipStream_t s) {
+  MgVecSet S{};
+  if (!vec_set(S, W, k, ncol, prec)) return -1;
+  const dim3 grid(gridx, ncol);
+  if (prec == 32) mg_mdot_kernel<32><<<grid, 256, 0, s>>>(S, k, w, npar, partial);
+  else mg_mdot_kernel<64><<<grid, 256, 0, s>>>(S, k, w, npar, partial);
+  mg_mdot_sum_kernel<<<k * ncol, 64, 0, s>>>(partial, iw2, gridx, coef);
+  return hipGetLastError() == hipSuccess ? 0 : -2;
+}
+
+int launch_mg_gcr_orth(int prec, const FieldRef* W, int k, FieldRef w, FieldRef r, int ncol, int npar, int gridx,
+                       const double* coef, double* red, hipStream_t s) {
+  MgVecSet S{};
+  if (!vec_set(S, W, k, ncol, prec)) return -1;
+  const dim3 grid(gridx, ncol);
+  if (prec == 32) mg_maxmy_kernel<32><<<grid, 256, 0, s>>>(S, k, w, r, npar, coef, red);
+  else mg_maxmy_kernel<64><<<grid, 256, 0, s>>>(S, k, w, r, npar, coef, red);
+  return hipGetLastError() == hipSuccess ? 0 : -2;
+}
+
+int launch_mg_gcr_solve(const double* alpha, const double* c, int n, int kmax, int ncol, double* y, hipStream_t s) {
+  mg_gcr_solve_kernel<<<(ncol + 63) / 64, 64, 0, s>>>(alpha, c, n, kmax, ncol, y);
+  return hipGetLastError() == hipSuccess ? 0 : -2;
+}
+
+int launch_mg_gcr_update(int prec, const FieldRef* Z, int k, FieldRef x, int ncol, int npar, int gridx,
+                         const double* y, hipStream_t s) {
+  MgVecSet S{};
+  if (!vec_set(S, Z, k, ncol, prec)) return -1;
+  const dim3 grid(gridx, ncol);
+  if (prec == 32) mg_xupdate_kernel<32><<<grid, 256, 0, s>>>(S, k, x, npar, y);
+  else mg_xupdate_kernel<64><<<grid, 256, 0, s>>>(S, k, x, npar, y);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 

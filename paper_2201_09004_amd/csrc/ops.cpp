@@ -66,7 +66,8 @@ void prof_flush(lq_ctx* c) {
 // once, each result written once): its algorithmic bytes for the timing records
 static int blas_transfers(int op) {
   switch (op) {
-    case OP_AXPY: case OP_AXMY: case OP_XPAY: case OP_XMY_NORM: case OP_LC_G5: case OP_PLC: return 3;
+    case OP_AXPY: case OP_AXMY: case OP_XPAY: case OP_XMY_NORM: case OP_GCR_R: case OP_LC_G5:
+    case OP_PLC: return 3;
     case OP_CG: return 6;
     case OP_BICG_XR: return 7;
     case OP_BICG_P: return 4;
@@ -76,7 +77,7 @@ static int blas_transfers(int op) {
 }
 static const char* blas_name(int op) {
   static const char* n[] = {"axpy", "axmy", "xpay", "cg", "bicg_xr", "bicg_p", "dot", "norm2", "dot_norm",
-                            "xmy_norm", "zero", "scale", "g5", "lc_g5", "copy", "plc"};
+                            "xmy_norm", "zero", "scale", "g5", "lc_g5", "copy", "gcr_r", "plc"};
   return op >= 0 && op < OP_NCOUNT ? n[op] : "op";
 }
 struct BlasProf {

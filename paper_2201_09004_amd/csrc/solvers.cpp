@@ -700,10 +700,10 @@ int gcr_mixed(Blas& bl, const Geom& g, const OpFn& M_hi, const OpFn& M_lo, int p
 }
 
 // Flexible GCR with sloppy inner vectors: every cycle of kmax directions runs
-// in precision plo (directions z_k = K(r), w_k = M z_k, their classical
-// Gram-Schmidt against the earlier directions in one pass,
-// the iterated residual and the cycle's correction), and ends with an FP64
-// update: x += correction, then r = b - M x in FP64 starts the next cycle (a
+// in precision plo (directions z_k = K(r), w_k = M z_k orthogonalised against
+// the earlier ones by classical Gram-Schmidt, the iterated residual), and ends
+// with an FP64 update: x += sum_k y_k z_k with y from the triangle of the
+// Gram-Schmidt coefficients, then r = b - M x in FP64 starts the next cycle (a
 // reliable update per cycle).  *steps counts the directions.  Three cycles
 // in a row that reduce the worst true residual by less than 10% end the solve
 // (LQ_ENOCONV).
@@ -713,7 +713,7 @@ int fgcr_mixed(Blas& bl, const Geom& g, const OpFn& M_hi, const OpFn& M_lo, cons
   const int n = b.ncol, nc = b.nc, npar = b.npar, par0 = b.par0;
   hipStream_t s = bl.s;
   Vec r = make_vec(g, 64, nc, n, npar, par0, s), q = make_vec(g, 64, nc, n, npar, par0, s);
-  Vec rs = make_vec(g, plo, nc, n, npar, par0, s), xs = make_vec(g, plo, nc, n, npar, par0, s);
+  Vec rs = make_vec(g, plo, nc, n, npar, par0, s);
   std::vector<Vec> Z, W;
   for (int k = 0; k < kmax; ++k) {
     Z.push_back(make_vec(g, plo, nc, n, npar, par0, s));
@@ -721,8 +721,11 @@ int fgcr_mixed(Blas& bl, const Geom& g, const OpFn& M_hi, const OpFn& M_lo, cons
     if (!Z.back().ok() || !W.back().ok()) return fail(LQ_ENOMEM, "gcr buffers");
   }
   State st(n, s);
-  DBuf cgs_part((size_t)8 * n * bl.gridx * 2 * sizeof(double), s), cgs_coef((size_t)8 * n * 2 * sizeof(double), s);
-  if (!r.ok() || !q.ok() || !rs.ok() || !xs.ok() || !st.ok() || !cgs_part.p || !cgs_coef.p)
+  // alpha[k][col], y[k][col], c[l][k][col] complex, iw2[k][col] real
+  const size_t row = 2 * sizeof(double) * (size_t)n;
+  DBuf dpart((size_t)8 * n * bl.gridx * 2 * sizeof(double), s), alpha(row * kmax, s), y(row * kmax, s),
+      cf(row * kmax * kmax, s), iw2(row / 2 * kmax, s);
+  if (!r.ok() || !q.ok() || !rs.ok() || !st.ok() || !dpart.p || !alpha.p || !y.p || !cf.p || !iw2.p)
     return fail(LQ_ENOMEM, "gcr buffers");
   for (int c = 0; c < n; ++c) {
     for (int k = 0; k < ST_STRIDE; ++k) st.h(c, k) = 0.0;
@@ -737,9 +740,6 @@ int fgcr_mixed(Blas& bl, const Geom& g, const OpFn& M_hi, const OpFn& M_lo, cons
       if (bb[c] > 0 && rr[c] > tol[c] * tol[c] * bb[c]) return false;
     return true;
   };
-  auto to_aux = [&]() -> int {
-    return launch_scalar(SC_DOT_TO_AUX, bl.partial, bl.gridx, n, st.d(), s) ? fail(LQ_EDEVICE, "scalar") : 0;
-  };
   auto true_res = [&]() -> int {
     int rc = M_hi(q, x);
     if (!rc) rc = bl.op(OP_XMY_NORM, &b, &q);
@@ -752,48 +752,44 @@ int fgcr_mixed(Blas& bl, const Geom& g, const OpFn& M_hi, const OpFn& M_lo, cons
     for (int c = 0; c < n; ++c) w = std::max(w, bb[c] > 0 ? rr[c] / bb[c] : 0.0);
     return w;
   };
+  const double vb = (double)vec_bytes(g, plo, nc, n, npar);
   int it = 0, stalled = 0;
   if ((e = true_res())) return e;
   while (it < maxiter && !converged()) {
     const double before = worst();
-    if ((e = vec_copy(rs, r)) || (e = vec_zero(xs))) return e;
-    for (int k = 0; k < kmax && it < maxiter; ++k) {
+    if ((e = vec_copy(rs, r))) return e;
+    int k = 0;
+    while (k < kmax && it < maxiter) {
       Vec& zk = Z[k];
       Vec& wk = W[k];
       if ((e = K(zk, rs, cnt)) || (e = M_lo(wk, zk))) return e;
-      // classical Gram-Schmidt against the earlier directions, up to 8 in one pass
+      // against the earlier directions, up to 8 in one pass; the last pass also gives <w, r> and |w|^2
       for (int j0 = 0; j0 < k; j0 += 8) {
-        FieldRef Wf[8], Zf[8];
+        FieldRef Wf[8];
         const int kk = std::min(8, k - j0);
-        for (int j = 0; j < kk; ++j) {
-          Wf[j] = W[j0 + j].f;
-          Zf[j] = Z[j0 + j].f;
-        }
-        // algorithmic bytes: w and the W_j read for the dots, then W_j, Z_j read and w, z read and written
-        const double vb = (double)wk.bytes > 0 ? (double)wk.bytes : (double)vec_bytes(g, plo, nc, n, npar);
-        Prof pc(bl.ctx, "mg_cgs", s, vb * (3.0 * kk + 5.0));
-        if (launch_mg_cgs(plo, Wf, Zf, kk, wk.f, zk.f, n, npar, bl.gridx, cgs_part.as<double>(),
-                          cgs_coef.as<double>(), s))
+        for (int j = 0; j < kk; ++j) Wf[j] = W[j0 + j].f;
+        // algorithmic bytes: w and the W_j for the dots, then W_j and r read and w read and written
+        Prof pc(bl.ctx, "mg_cgs", s, vb * (2.0 * kk + 4.0));
+        double* c = cf.as<double>() + ((size_t)k * kmax + j0) * 2 * n;
+        if (launch_mg_gcr_dots(plo, Wf, kk, wk.f, n, npar, bl.gridx, dpart.as<double>(),
+                               iw2.as<double>() + (size_t)j0 * n, c, s) ||
+            launch_mg_gcr_orth(plo, Wf, kk, wk.f, rs.f, n, npar, bl.gridx, c, j0 + 8 >= k ? bl.partial : nullptr, s))
           return fail(LQ_EDEVICE, "gram-schmidt");
       }
-      std::vector<double> ww;
-      if ((e = col_norms(bl, wk, ww)) || (e = st.pull())) return e;
+      if (k == 0 && (e = bl.op(OP_DOT_NORM, &wk, &rs))) return e;
+      // alpha = <w, r> / |w|^2: r -= alpha w
+      if (launch_scalar_gcr(bl.partial, bl.gridx, n, st.d(), alpha.as<double>() + (size_t)k * 2 * n,
+                            iw2.as<double>() + (size_t)k * n, s))
+        return fail(LQ_EDEVICE, "scalar");
+      if ((e = bl.op(OP_GCR_R, &wk, &rs, nullptr, nullptr, nullptr, st.d(), ST_ALPHA, ST_ALPHA))) return e;
+      if (launch_scalar(SC_SET_RR, bl.partial, bl.gridx, n, st.d(), s)) return fail(LQ_EDEVICE, "scalar");
+      if ((e = st.pull())) return e;
       for (int c = 0; c < n; ++c) {
-        const double inv = ww[c] > 0 ? 1.0 / std::sqrt(ww[c]) : 0.0;
-        if (!std::isfinite(inv)) return fail(LQ_ENUMERIC, "GCR: non-finite direction norm");
-        st.h(c, ST_AUX) = inv;
-        st.h(c, ST_AUX + 1) = 0.0;
+        if (st.h(c, ST_FLAG) == 2.0) return fail(LQ_ENUMERIC, "GCR: non-finite direction");
+        rr[c] = st.h(c, ST_RR);
       }
-      if ((e = st.push())) return e;
-      if ((e = bl.op(OP_SCALE, &wk, nullptr, nullptr, nullptr, nullptr, st.d(), ST_AUX, ST_AUX)) ||
-          (e = bl.op(OP_SCALE, &zk, nullptr, nullptr, nullptr, nullptr, st.d(), ST_AUX, ST_AUX)))
-        return e;
-      if ((e = bl.op(OP_DOT, &wk, &rs)) || (e = to_aux())) return e;
-      if ((e = bl.op(OP_AXPY, &zk, &xs, nullptr, nullptr, nullptr, st.d(), ST_AUX, ST_AUX)) ||
-          (e = bl.op(OP_AXMY, &wk, &rs, nullptr, nullptr, nullptr, st.d(), ST_AUX, ST_AUX)) ||
-          (e = col_norms(bl, rs, rr)))
-        return e;
       ++it;
+      ++k;
       if (verbose()) {
         double wr = 0.0;
         for (int c = 0; c < n; ++c) wr = std::max(wr, bb[c] > 0 ? std::sqrt(rr[c] / bb[c]) : 0.0);
@@ -801,8 +797,16 @@ int fgcr_mixed(Blas& bl, const Geom& g, const OpFn& M_hi, const OpFn& M_lo, cons
       }
       if (converged()) break;
     }
-    // the cycle's correction in FP64, then the true residual
-    if (launch_axpy_mixed(x.f, 64, xs.f, plo, nc, n, npar, g.Vh, s)) return fail(LQ_EDEVICE, "axpy");
+    // the cycle's correction, then the true residual in FP64
+    if (launch_mg_gcr_solve(alpha.as<double>(), cf.as<double>(), k, kmax, n, y.as<double>(), s))
+      return fail(LQ_EDEVICE, "gcr coefficients");
+    for (int j0 = 0; j0 < k; j0 += 8) {
+      FieldRef Zf[8];
+      const int kk = std::min(8, k - j0);
+      for (int j = 0; j < kk; ++j) Zf[j] = Z[j0 + j].f;
+      if (launch_mg_gcr_update(plo, Zf, kk, x.f, n, npar, bl.gridx, y.as<double>() + (size_t)j0 * 2 * n, s))
+        return fail(LQ_EDEVICE, "gcr update");
+    }
     ++cnt.reliable;
     if ((e = true_res())) return e;
     // three cycles in a row that reduce the worst true residual by less than 10% end the solve
