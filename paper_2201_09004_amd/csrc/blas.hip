@@ -151,6 +151,18 @@ __global__ void __launch_bounds__(256) blas_kernel(BlasArgs A) {
       for (int k = 0; k < NC; ++k) b[k] = b[k] - c0 * a[k];
       IOt::store(A.f[1], blk, cb, b);
       red[0] += norm_acc<R, NC>(b);
+    } else if constexpr (OP == OP_MR0 || OP == OP_MR) {
+      cx<R> e[NC];
+      IOt::load(A.f[0], blk, cb, a);
+      IOt::load(A.f[1], blk, cb, b);
+      if constexpr (OP == OP_MR) IOt::load(A.f[2], blk, cb, e);
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        e[k] = OP == OP_MR ? e[k] + c0 * a[k] : c0 * a[k];
+        a[k] = a[k] - c0 * b[k];
+      }
+      IOt::store(A.f[2], blk, cb, e);
+      IOt::store(A.f[0], blk, cb, a);
     } else if constexpr (OP == OP_ZERO) {
 #pragma unroll
       for (int k = 0; k < NC; ++k) a[k] = {0, 0};
@@ -204,7 +216,7 @@ static void blas_dispatch(const BlasArgs& A, dim3 grid, dim3 block, hipStream_t 
   switch (A.op) {
     LQ_OPC(OP_AXPY) LQ_OPC(OP_AXMY) LQ_OPC(OP_XPAY) LQ_OPC(OP_CG) LQ_OPC(OP_BICG_XR) LQ_OPC(OP_BICG_P)
     LQ_OPC(OP_DOT) LQ_OPC(OP_NORM2) LQ_OPC(OP_DOT_NORM) LQ_OPC(OP_XMY_NORM) LQ_OPC(OP_ZERO) LQ_OPC(OP_SCALE)
-    LQ_OPC(OP_G5) LQ_OPC(OP_LC_G5) LQ_OPC(OP_COPY) LQ_OPC(OP_GCR_R) LQ_OPC(OP_PLC)
+    LQ_OPC(OP_G5) LQ_OPC(OP_LC_G5) LQ_OPC(OP_COPY) LQ_OPC(OP_GCR_R) LQ_OPC(OP_MR0) LQ_OPC(OP_MR) LQ_OPC(OP_PLC)
     default: break;
   }
 #undef LQ_OPC

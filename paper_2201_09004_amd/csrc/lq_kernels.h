@@ -15,9 +15,10 @@ namespace lq {
 // |out|^2 written as wave partials red[(col * ntile + tile) * 4 + k]
 // (ntile = 64-site tiles of the launch).  EPI_CLOVINV_XPAY: A^{-1} (x + k hop)
 // (the even-odd source and the odd-site reconstruction of the twisted clover).
-// EPI_XPAY_NORM: EPI_XPAY plus |out|^2 per column in red[... + 0].
+// EPI_XPAY_NORM: EPI_XPAY plus |out|^2 per column in red[... + 0].  EPI_RESID:
+// v - (A x + k hop) (residual of the twisted clover).  EPI_CLOVINV_ACC: v + A^{-1} (x + k hop).
 enum { EPI_HOP = 0, EPI_XPAY, EPI_XPAY_G5, EPI_CLOVINV, EPI_XMY_CLOVINV, EPI_SITE, EPI_CHEB, EPI_XMY_RTS,
-       EPI_CLOVINV_XPAY, EPI_XPAY_NORM };
+       EPI_CLOVINV_XPAY, EPI_XPAY_NORM, EPI_RESID, EPI_CLOVINV_ACC };
 
 struct WilsonArgs {
   Geom g;
@@ -79,6 +80,8 @@ int launch_unpack_field(const Geom& g, FieldRef in, int prec, int ncol, int nc, 
                         hipStream_t s, bool zero = false);
 int launch_convert(FieldRef dst, int pdst, FieldRef src, int psrc, int nc, int ncol, int npar, int Vh,
                    hipStream_t s);
+// one parity of dst (npar = 2) = or += src (npar = 1), same precision (64 or 32), Wilson-type
+int launch_parity_put(FieldRef dst, int par, FieldRef src, int prec, int ncol, int Vh, bool add, hipStream_t s);
 double link_maxabs(const double* aos, int64_t n, hipStream_t s);
 
 // ------------------------------------------------------------ clover (FP64 build)
@@ -104,6 +107,8 @@ enum {
   OP_LC_G5,      // f2 = c0 f0 + c1 g5 f1 (Wilson only)
   OP_COPY,       // f1 = f0
   OP_GCR_R,      // f1 -= c0 f0 ; red |f1|^2
+  OP_MR0,        // f2 = c0 f0 ; f0 -= c0 f1
+  OP_MR,         // f2 += c0 f0 ; f0 -= c0 f1
   OP_PLC,        // f2 = p0 f0 + p1 (p2 f1 + p3 g5 f1), real p0..p3 per column from pcol (Wilson only)
   OP_NCOUNT
 };

@@ -70,14 +70,15 @@ static int blas_transfers(int op) {
     case OP_PLC: return 3;
     case OP_CG: return 6;
     case OP_BICG_XR: return 7;
-    case OP_BICG_P: return 4;
+    case OP_BICG_P: case OP_MR0: return 4;
+    case OP_MR: return 5;
     case OP_DOT: case OP_DOT_NORM: case OP_SCALE: case OP_G5: case OP_COPY: return 2;
     default: return 1;
   }
 }
 static const char* blas_name(int op) {
   static const char* n[] = {"axpy", "axmy", "xpay", "cg", "bicg_xr", "bicg_p", "dot", "norm2", "dot_norm",
-                            "xmy_norm", "zero", "scale", "g5", "lc_g5", "copy", "gcr_r", "plc"};
+                            "xmy_norm", "zero", "scale", "g5", "lc_g5", "copy", "gcr_r", "mr0", "mr", "plc"};
   return op >= 0 && op < OP_NCOUNT ? n[op] : "op";
 }
 struct BlasProf {
@@ -500,14 +501,15 @@ static int run_wilson(OpEnv& e, WilsonArgs& A, int n_fields, int clov_mats, int 
   if (!A.links) return fail(LQ_EDEVICE, "links not packed");
   const int nsite = A.par_out == 2 ? 2 * A.g.Vh : A.g.Vh;
   static const char* epi_names[] = {"hop", "xpay", "xpay_g5", "clovinv", "xmy", "site", "cheb", "xmyt", "clovinv_x",
-                                    "xpayn"};
+                                    "xpayn", "resid", "clovinv_a"};
   char name[48];
   snprintf(name, sizeof(name), "wilson%d_%s", A.prec, epi_names[A.epi]);
   char key[160];
   snprintf(key, sizeof(key), "%s_r%d_d%d_n%d_v%d_p%d", name, A.recon, A.dag, col_bucket(A.ncol), A.g.Vh, A.par_out);
   const bool blocked = A.dag ? A.epi == EPI_XPAY || A.epi == EPI_SITE : (A.epi == EPI_CLOVINV || A.epi == EPI_XMY_CLOVINV || A.epi == EPI_XPAY ||
                                   A.epi == EPI_XPAY_G5 || A.epi == EPI_CHEB || A.epi == EPI_XMY_RTS ||
-                                  A.epi == EPI_SITE || A.epi == EPI_CLOVINV_XPAY || A.epi == EPI_XPAY_NORM);
+                                  A.epi == EPI_SITE || A.epi == EPI_CLOVINV_XPAY || A.epi == EPI_XPAY_NORM ||
+                                  A.epi == EPI_RESID || A.epi == EPI_CLOVINV_ACC);
   // one hop per wave is worth timing while one thread per site leaves SIMDs
   // without a wave or with few (at most 4 per SIMD).  Between events, one thread
   // per site against one hop per wave, FP64 twisted-clover D: 64 waves 27 and 19
@@ -561,6 +563,26 @@ int wilson_D(OpEnv& e, int prec, Vec& out, const Vec& in, bool dag, double* red)
   A.red = red;
   A.a = 4.0 + e.act.m;
   return run_wilson(e, A, 3, 0, red ? 96 : 48);
+}
+
+int tm_residual(OpEnv& e, int prec, Vec& out, const Vec& b, const Vec& in) {
+  int r = ensure_links(e, prec);
+  if (!r) r = ensure_clover(e, prec);
+  if (r) return r;
+  WilsonArgs A{};
+  A.prec = prec;
+  A.par_out = 2;
+  A.ncol = in.ncol;
+  A.links = links_for(e, prec);
+  A.in = in.f;
+  A.out = out.f;
+  A.x = in.f;
+  A.v = b.f;
+  A.k_hop = -0.5;
+  A.epi = EPI_RESID;
+  A.clov = get_clover(e)->H[pidx(prec)];
+  A.mu_tw = e.act.mu;
+  return run_wilson(e, A, 4, 1, 528);
 }
 
 int wilson_hop(OpEnv& e, int prec, Vec& out, const Vec& in) {
@@ -644,34 +666,28 @@ int tm_schur_source(OpEnv& e, Vec& bhat_e, const Vec& b) {
   return run_wilson(e, A, 3, 2, 600);
 }
 
-int tm_schur_reconstruct(OpEnv& e, Vec& x, const Vec& x_e, const Vec& b) {
+int tm_schur_reconstruct(OpEnv& e, Vec& x, const Vec& x_e, const Vec& b, bool add) {
   const int prec = x.prec;
   int r = ensure_links(e, prec);
   if (!r) r = ensure_clover(e, prec);
   if (r) return r;
   const Clover* c = get_clover(e);
+  // x_e into (onto) the even half of x
+  if (launch_parity_put(x.f, 0, x_e.f, prec, b.ncol, e.f->g.Vh, add, e.s)) return fail(LQ_EDEVICE, "even half");
+  // x_o = A_oo^-1 (b_o - D_oe x_e) = A_oo^-1 (b_o + 1/2 hop(x_e)) in one stencil
   WilsonArgs A{};
   A.prec = prec;
   A.ncol = b.ncol;
   A.links = links_for(e, prec);
-  // x_e into the even half of x (hop scaled by zero)
   A.in = x_e.f;
   A.out = x.f;
-  A.x = x_e.f;
-  A.a = 1.0;
-  A.k_hop = 0.0;
-  A.par_out = 0;
-  A.epi = EPI_XPAY;
-  r = run_wilson(e, A, 2, 0, 0);
-  if (r) return r;
-  // x_o = A_oo^-1 (b_o - D_oe x_e) = A_oo^-1 (b_o + 1/2 hop(x_e)) in one stencil
-  A.out = x.f;
   A.x = b.f;
+  A.v = x.f;
   A.clov_inv = c->Ainv[pidx(prec)];
   A.k_hop = 0.5;
   A.par_out = 1;
-  A.epi = EPI_CLOVINV_XPAY;
-  return run_wilson(e, A, 3, 2, 600);
+  A.epi = add ? EPI_CLOVINV_ACC : EPI_CLOVINV_XPAY;
+  return run_wilson(e, A, add ? 4 : 3, 2, 600);
 }
 
 // ------------------------------------------------------------------ overlap

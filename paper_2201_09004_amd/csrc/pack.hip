@@ -341,6 +341,38 @@ __global__ void axpy_mixed_kernel(FieldRef y, FieldRef x, int64_t nslot, int Vh)
   IO<P1, NC>::store(y, blk, cb, w);
 }
 
+// one parity of dst (npar = 2) = (ADD: +=) src (npar = 1)
+template <int P, bool ADD>
+__global__ void parity_put_kernel(FieldRef dst, int par, FieldRef src, int64_t n, int Vh) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int cb = (int)(i % Vh);
+  const int64_t col = i / Vh;
+  using R = typename RealOf<P>::T;
+  cx<R> v[12];
+  IO<P, 12>::load(src, col, cb, v);
+  if constexpr (ADD) {
+    cx<R> w[12];
+    IO<P, 12>::load(dst, col * 2 + par, cb, w);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) v[k] = w[k] + v[k];
+  }
+  IO<P, 12>::store(dst, col * 2 + par, cb, v);
+}
+
+int launch_parity_put(FieldRef dst, int par, FieldRef src, int prec, int ncol, int Vh, bool add, hipStream_t s) {
+  const int64_t n = (int64_t)ncol * Vh;
+  if (n == 0) return 0;
+  if (prec == 16 || dst.npar != 2 || src.npar != 1) return -1;
+  const int bs = 256;
+  const int nb = (int)((n + bs - 1) / bs);
+  if (prec == 64 && add) parity_put_kernel<64, true><<<nb, bs, 0, s>>>(dst, par, src, n, Vh);
+  else if (prec == 64) parity_put_kernel<64, false><<<nb, bs, 0, s>>>(dst, par, src, n, Vh);
+  else if (add) parity_put_kernel<32, true><<<nb, bs, 0, s>>>(dst, par, src, n, Vh);
+  else parity_put_kernel<32, false><<<nb, bs, 0, s>>>(dst, par, src, n, Vh);
+  return hipGetLastError() == hipSuccess ? 0 : -3;
+}
+
 #define LQ_PAIR_DISPATCH(KERNEL, P1_, P2_, NC_, ...)                                              \
   do {                                                                                             \
     const int key = (P1_) * 1000 + (P2_);                                                          \

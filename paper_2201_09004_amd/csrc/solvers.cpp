@@ -193,7 +193,7 @@ using FusedFn = std::function<int(Vec& out, const Vec& in, int mode, double* red
 // receive views of the active columns.
 int cg_mixed(Blas& bl, const Geom& g, const OpFn& A_hi, const OpFn& A_lo, int plo, Vec& x, Vec& b,
              const std::vector<double>& tol_in, int maxiter, double delta, Counters& cnt, ColParam* cp = nullptr,
-             const FusedFn* A_fused = nullptr) {
+             const FusedFn* A_fused = nullptr, bool zero_guess = false) {
   const int n = b.ncol, nc = b.nc, npar = b.npar, par0 = b.par0;
   hipStream_t s = bl.s;
   // A_fused: the sloppy operator with <p, A p> from its stencil epilogue
@@ -214,7 +214,12 @@ int cg_mixed(Blas& bl, const Geom& g, const OpFn& A_hi, const OpFn& A_lo, int pl
   if (e) return e;
   int na = n;  // active columns occupy slots [0, na)
   // r = b - A x (FP64) on the active columns
-  auto true_res = [&]() -> int {
+  auto true_res = [&](bool zero = false) -> int {
+    if (zero) {  // x = 0
+      if (int rc = vec_copy(r, b)) return rc;
+      if (int rc = bl.op(OP_NORM2, &r)) return rc;
+      return launch_scalar(SC_SET_RR, bl.partial, bl.gridx, na, st.d(), s) ? fail(LQ_EDEVICE, "scalar") : 0;
+    }
     Vec qv = view(q64, 0, na), xv = view(x, 0, na), bv = view(b, 0, na);
     int rr = A_hi(qv, xv);
     if (rr) return rr;
@@ -235,7 +240,7 @@ int cg_mixed(Blas& bl, const Geom& g, const OpFn& A_hi, const OpFn& A_lo, int pl
     st.h(c, ST_ACTIVE) = 1.0;
   }
   if ((e = st.push())) return e;
-  if ((e = true_res())) return e;
+  if ((e = true_res(zero_guess))) return e;
   if ((e = vec_copy(rs, r)) || (e = vec_copy(p, r)) || (e = vec_zero(xs))) return e ? e : fail(LQ_EDEVICE, "copy");
   if ((e = st.pull())) return e;
   for (int c = 0; c < n; ++c) {
@@ -412,11 +417,11 @@ int cg_mixed(Blas& bl, const Geom& g, const OpFn& A_hi, const OpFn& A_lo, int pl
 
 // Mixed-precision BiCGStab with reliable updates for a non-Hermitian M.
 // M_fused (optional): the sloppy operator with the fused reductions <out, in>
-// and |out|^2 (mode 2) as partials over 64-site tiles.
+// and |out|^2 (mode 2) as partials over 64-site tiles.  zero_guess: x is zero.
 
 int bicgstab_mixed(Blas& bl, const Geom& g, const OpFn& M_hi, const OpFn& M_lo, int plo, Vec& x, Vec& b,
                    const std::vector<double>& tol_in, int maxiter, double delta, Counters& cnt,
-                   const FusedFn* M_fused = nullptr) {
+                   const FusedFn* M_fused = nullptr, bool zero_guess = false) {
   const int n = b.ncol, nc = b.nc, npar = b.npar, par0 = b.par0;
   hipStream_t s = bl.s;
   const int fused_tiles = (npar * g.Vh + 63) / 64;
@@ -450,8 +455,8 @@ int bicgstab_mixed(Blas& bl, const Geom& g, const OpFn& M_hi, const OpFn& M_lo, 
     return 0;
   };
   // (re)start: r = b - M x, rhat = r, p = r, rho = <rhat, r>
-  auto restart = [&]() -> int {
-    int rr = true_res();
+  auto restart = [&](bool zero = false) -> int {
+    int rr = zero ? vec_copy(r, b) : true_res();
     if (rr) return rr;
     Vec rv = V(r), rsv = V(rs), rhv = V(rhat), pv = V(p);
     if ((rr = vec_copy(rsv, rv)) || (rr = vec_copy(rhv, rv)) || (rr = vec_copy(pv, rv))) return rr;
@@ -465,7 +470,7 @@ int bicgstab_mixed(Blas& bl, const Geom& g, const OpFn& M_hi, const OpFn& M_lo, 
   }
   if ((e = st.push())) return e;
   if ((e = vec_zero(xs))) return e;
-  if ((e = restart())) return e;
+  if ((e = restart(zero_guess))) return e;
   if ((e = st.pull())) return e;
   for (int c = 0; c < n; ++c) {
     maxrr[c] = rr_chk[c] = st.h(c, ST_RR);
@@ -687,7 +692,8 @@ int gcr_mixed(Blas& bl, const Geom& g, const OpFn& M_hi, const OpFn& M_lo, int p
     int e = vec_zero(z);
     if (e) return e;
     Counters inner;
-    const int ri = bicgstab_mixed(bl, g, M_hi, M_lo, plo, z, r, inner_tolv, inner_iters, delta, inner, M_fused);
+    const int ri = bicgstab_mixed(bl, g, M_hi, M_lo, plo, z, r, inner_tolv, inner_iters, delta, inner, M_fused,
+                                  true);
     if (ri != LQ_OK && ri != LQ_ENOCONV) return ri;
     c.iters += inner.iters;
     return 0;
@@ -833,7 +839,7 @@ struct MgCycle {
   Blas& bl;  // fine-level reductions (full lattice)
   int n;
   Vec r32, e32, t32, bc, xc, be, xe, to, ue, tmp64, tmp32;
-  Vec she, sre, sue, sto, sde;  // smoother: even correction, residual, M_hat residual; odd temporary; full correction
+  Vec she, sre, sue, sto;  // smoother: even correction, residual, M_hat residual; odd temporary
   Vec spre;                     // pre-smoothing correction (nu_pre > 0)
   Blas blc, ble;
   DBuf red;
@@ -863,7 +869,6 @@ struct MgCycle {
     sre = make_vec(g, 32, 12, n, 1, 0, s);
     sue = make_vec(g, 32, 12, n, 1, 0, s);
     sto = make_vec(g, 32, 12, n, 1, 1, s);
-    sde = make_vec(g, 32, 12, n, 2, 0, s);
     if (h.nu_pre > 0) {
       spre = make_vec(g, 32, 12, n, 2, 0, s);
       if (!spre.ok()) return fail(LQ_ENOMEM, "multigrid cycle buffers");
@@ -872,7 +877,7 @@ struct MgCycle {
     red = DBuf(sizeof(double) * 4 * (size_t)tiles * n, s);
     if ((fp64_io && (!r32.ok() || !e32.ok())) || !t32.ok() || !bc.ok() || !xc.ok() || !be.ok() || !xe.ok() ||
         !ue.ok() || !to.ok() || !tmp64.ok() || !tmp32.ok() || !she.ok() || !sre.ok() || !sue.ok() || !sto.ok() ||
-        !sde.ok() || !red.p || !st.ok())
+        !red.p || !st.ok())
       return fail(LQ_ENOMEM, "multigrid cycle buffers");
     for (int c = 0; c < n; ++c) {
       for (int k = 0; k < ST_STRIDE; ++k) st.h(c, k) = 0.0;
@@ -883,19 +888,23 @@ struct MgCycle {
     if (!e) e = blas_prepare(env.ctx, ble, g, 1, n, s);
     return e;
   }
-  // sde = the correction of nu minimal-residual steps on the even-odd system
-  // for the full-lattice residual res (zero start; res is left unchanged)
-  int smooth(Vec& res, int nu) {
+  // the correction of nu minimal-residual steps on the even-odd system for the
+  // full-lattice residual res (zero start; res is left unchanged): added to out,
+  // or written to it
+  int smooth(Vec& res, int nu, Vec& out, bool add) {
     int e = 0;
-    if ((e = tm_schur_source(env, sre, res)) || (e = vec_zero(she))) return e;
+    if ((e = tm_schur_source(env, sre, res))) return e;
     for (int k = 0; k < nu; ++k) {
       if ((e = tm_schur(env, 32, sue, sre, sto, 2, red.as<double>()))) return e;
       if (launch_scalar(SC_BICG_OMEGA, red.as<double>(), tiles, n, st.d(), env.s)) return fail(LQ_EDEVICE, "scalar");
-      if ((e = ble.op(OP_AXPY, &sre, &she, nullptr, nullptr, nullptr, st.d(), ST_OMEGA, ST_OMEGA))) return e;
-      if (k + 1 < nu && (e = ble.op(OP_AXMY, &sue, &sre, nullptr, nullptr, nullptr, st.d(), ST_OMEGA, ST_OMEGA)))
-        return e;
+      // e_e += omega t and t -= omega u in one pass; the last step needs e_e alone
+      if (k > 0 && k + 1 == nu)
+        e = ble.op(OP_AXPY, &sre, &she, nullptr, nullptr, nullptr, st.d(), ST_OMEGA, ST_OMEGA);
+      else
+        e = ble.op(k == 0 ? OP_MR0 : OP_MR, &sre, &sue, &she, nullptr, nullptr, st.d(), ST_OMEGA, ST_OMEGA);
+      if (e) return e;
     }
-    return tm_schur_reconstruct(env, sde, she, res);
+    return tm_schur_reconstruct(env, out, she, res, add);
   }
   // z = K r; r and z in FP32 are used in place, FP64 ones are converted
   int operator()(Vec& z, Vec& r) {
@@ -907,8 +916,7 @@ struct MgCycle {
     // optional pre-smoothing: its correction e_pre, and the coarse level sees r - D e_pre
     Vec* res = &rin;
     if (h.nu_pre > 0) {
-      if ((e = smooth(rin, h.nu_pre)) || (e = vec_copy(spre, sde))) return e;
-      if ((e = wilson_D(env, 32, t32, spre, false)) || (e = bl.op(OP_XMY_NORM, &rin, &t32))) return e;
+      if ((e = smooth(rin, h.nu_pre, spre, false)) || (e = tm_residual(env, 32, t32, rin, spre))) return e;
       res = &t32;
     }
     // coarse solve on the even aggregates: (1 - A_ee^-1 D_eo A_oo^-1 D_oe) x_e = bhat_e
@@ -919,14 +927,14 @@ struct MgCycle {
       return mg_schur_op(env, h, o, i, t);
     };
     std::vector<double> tolc(n, h.coarse_tol);
-    const int rc = bicgstab_mixed(blc, h.gc, S, S, 32, xe, be, tolc, h.coarse_maxiter, 0.1, coarse, nullptr);
+    const int rc = bicgstab_mixed(blc, h.gc, S, S, 32, xe, be, tolc, h.coarse_maxiter, 0.1, coarse, nullptr,
+                                  true);
     if (rc != LQ_OK && rc != LQ_ENOCONV) return rc;
     if ((e = mg_schur_reconstruct(env, h, xc, xe, to))) return e;
     if ((e = mg_prolong(env, h, xc, ev))) return e;
     if (h.nu_pre > 0 && (e = bl.opi(OP_AXPY, &spre, &ev, nullptr, 1.0))) return e;
     // fine-level smoothing on the residual of the correction so far, on the even-odd system
-    if ((e = wilson_D(env, 32, t32, ev, false)) || (e = bl.op(OP_XMY_NORM, &rin, &t32))) return e;
-    if ((e = smooth(t32, h.nu_post)) || (e = bl.opi(OP_AXPY, &sde, &ev, nullptr, 1.0))) return e;
+    if ((e = tm_residual(env, 32, t32, rin, ev)) || (e = smooth(t32, h.nu_post, ev, true))) return e;
     ++cycles;
     return z.prec == 32 ? 0 : vec_copy(z, e32);
   }
@@ -955,7 +963,7 @@ int mg_null_vectors(OpEnv& env, Vec& w, int passes, int maxiter, double tol, Cou
   std::vector<double> tolv(n, tol), nn;
   for (int p = 0; p < passes; ++p) {
     if ((e = tm_schur_source(env, bh, w)) || (e = vec_zero(xe))) return e;
-    const int rs = bicgstab_mixed(ble, g, M64, M32, 32, xe, bh, tolv, maxiter, 0.1, cnt, &Mf);
+    const int rs = bicgstab_mixed(ble, g, M64, M32, 32, xe, bh, tolv, maxiter, 0.1, cnt, &Mf, true);
     if (rs != LQ_OK && rs != LQ_ENOCONV) return rs;
     if ((e = tm_schur_reconstruct(env, x, xe, w)) || (e = col_norms(bl, x, nn))) return e;
     for (int c = 0; c < n; ++c) {
@@ -1422,7 +1430,7 @@ int solve(lq_ctx* c, const lq_action* act, lq_field* f, const lq_params* prm, in
                            ? gcr_mixed(ble, g, M64, Mlo, plo, xe, bh, tol_s, maxiter, delta, cnt,
                                        fuse ? &Mfused : nullptr, 8, 0.1, 50)
                            : bicgstab_mixed(ble, g, M64, Mlo, plo, xe, bh, tol_s, maxiter, delta, cnt,
-                                            fuse ? &Mfused : nullptr);
+                                            fuse ? &Mfused : nullptr, pass == 0 && !prm->use_initial_guess);
         if (rs != LQ_OK && rs != LQ_ENOCONV) return rs;
         if ((e = tm_schur_reconstruct(env, x, xe, b))) return e;
         if ((e = rel_residual(bl, D64, x, b, res, g))) return e;
@@ -1464,7 +1472,7 @@ int solve(lq_ctx* c, const lq_action* act, lq_field* f, const lq_params* prm, in
       std::vector<double> tol_n(n_rhs, 0.1 * tol);
       for (int pass = 0; pass < 6; ++pass) {
         const int rs = cg_mixed(bl, g, N64, Nlo, plo, x, bn, tol_n, maxiter, delta, cnt, nullptr,
-                                kind == LQ_WILSON ? &Nfused : nullptr);
+                                kind == LQ_WILSON ? &Nfused : nullptr, pass == 0 && !prm->use_initial_guess);
         if (rs != LQ_OK && rs != LQ_ENOCONV) return rs;
         if ((e = rel_residual(bl, D64, x, b, res, g))) return e;
         worst = *std::max_element(res.begin(), res.end());
@@ -1661,7 +1669,8 @@ int solve(lq_ctx* c, const lq_action* act, lq_field* f, const lq_params* prm, in
     ColParam cpm{m2col, dm2.as<double>(), s};  // m^2 per column follows the solver's reordering
     std::vector<double> res;
     for (int pass = 0; pass < 4; ++pass) {
-      const int rs = cg_mixed(ble, g, A64, Alo, plo, y, brep, tolv, maxiter, delta, cnt, &cpm, &Afused);
+      const int rs = cg_mixed(ble, g, A64, Alo, plo, y, brep, tolv, maxiter, delta, cnt, &cpm, &Afused,
+                              pass == 0 && nsh == 1 && !prm->use_initial_guess);
       if (rs != LQ_OK && rs != LQ_ENOCONV) return rs;
       status = rs;
       if ((e = rel_residual(ble, A64, y, brep, res, g))) return e;

@@ -11,6 +11,8 @@
 //   EPI_CLOVINV     out = A^{-1} (k hop)              (first half of the Schur operator)
 //   EPI_CLOVINV_XPAY out = A^{-1} (x + k hop)         (even-odd source, odd-site reconstruction)
 //   EPI_XMY_CLOVINV out = x - A^{-1} (k hop)          (second half)
+//   EPI_CLOVINV_ACC out = v + A^{-1} (x + k hop)      (the same, onto the multigrid correction)
+//   EPI_RESID       out = v - (A x + k hop)           (residual of the full twisted-clover D)
 //   EPI_SITE        out = A x + k hop,  A = H + i mu g5 (full twisted-clover D)
 //   EPI_CHEB        out = s1 g5 (a x + k hop) + ck v + s2 b1 - b2   (one Clenshaw step)
 // where x, v, b1, b2 are fields of the output parity.  The time-boundary
@@ -271,7 +273,7 @@ wilson_kernel(WilsonArgs A) {
 #pragma unroll
     for (int i = 0; i < 12; ++i) acc[r][i] = k * acc[r][i];
 
-  if constexpr (EPI == EPI_CLOVINV_XPAY) {
+  if constexpr (EPI == EPI_CLOVINV_XPAY || EPI == EPI_CLOVINV_ACC) {
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       if (r >= nv) continue;
@@ -281,7 +283,7 @@ wilson_kernel(WilsonArgs A) {
       for (int i = 0; i < 12; ++i) acc[r][i] = acc[r][i] + x[i];
     }
   }
-  if constexpr (EPI == EPI_CLOVINV || XMY || EPI == EPI_CLOVINV_XPAY) {
+  if constexpr (EPI == EPI_CLOVINV || XMY || EPI == EPI_CLOVINV_XPAY || EPI == EPI_CLOVINV_ACC) {
     apply_full6_nr<P, NR>(A.clov_inv, A.g.Vh, par, 0, cb, nv, acc, 0);
     apply_full6_nr<P, NR>(A.clov_inv, A.g.Vh, par, 1, cb, nv, acc, 6);
   }
@@ -296,6 +298,11 @@ wilson_kernel(WilsonArgs A) {
     if constexpr (EPI == EPI_HOP || EPI == EPI_CLOVINV || EPI == EPI_CLOVINV_XPAY) {
 #pragma unroll
       for (int i = 0; i < 12; ++i) out[i] = acc[r][i];
+    } else if constexpr (EPI == EPI_CLOVINV_ACC) {
+      cx<R> v[12];
+      IO<P, 12>::template load<true>(A.v, blk_index(A.v, col, par), cb, v);
+#pragma unroll
+      for (int i = 0; i < 12; ++i) out[i] = v[i] + acc[r][i];
     } else if constexpr (XMY) {
       cx<R> x[12];
       IO<P, 12>::template load<true>(A.x, blk_index(A.x, col, par), cb, x);
@@ -341,7 +348,7 @@ wilson_kernel(WilsonArgs A) {
 #pragma unroll
         for (int i = 0; i < 12; ++i) out[i] = out[i] - v[i];
       }
-    } else if constexpr (EPI == EPI_SITE) {
+    } else if constexpr (EPI == EPI_SITE || EPI == EPI_RESID) {
       cx<R> x[12];
       IO<P, 12>::template load<true>(A.x, blk_index(A.x, col, par), cb, x);
       apply_herm6<P>(A.clov, A.g.Vh, par, 0, cb, x, out);
@@ -351,6 +358,11 @@ wilson_kernel(WilsonArgs A) {
       for (int i = 0; i < 6; ++i) out[i] = out[i] + mu * times_i(x[i]) + acc[r][i];
 #pragma unroll
       for (int i = 6; i < 12; ++i) out[i] = out[i] - mu * times_i(x[i]) + acc[r][i];
+      if constexpr (EPI == EPI_RESID) {
+        IO<P, 12>::template load<true>(A.v, blk_index(A.v, col, par), cb, x);
+#pragma unroll
+        for (int i = 0; i < 12; ++i) out[i] = x[i] - out[i];
+      }
     }
     if (live) IO<P, 12>::template store<true>(A.out, blk_index(A.out, col, par), cb, out);
   }
@@ -603,7 +615,8 @@ inline void launch_one(const WilsonArgs& A, int bs, hipStream_t s) {
 // epilogues with register-blocked variants (NR > 1)
 constexpr bool epi_blocked(int epi) {
   return epi == EPI_CLOVINV || epi == EPI_XMY_CLOVINV || epi == EPI_XPAY || epi == EPI_XPAY_G5 || epi == EPI_CHEB ||
-         epi == EPI_XMY_RTS || epi == EPI_SITE || epi == EPI_CLOVINV_XPAY || epi == EPI_XPAY_NORM;
+         epi == EPI_XMY_RTS || epi == EPI_SITE || epi == EPI_CLOVINV_XPAY || epi == EPI_XPAY_NORM ||
+         epi == EPI_RESID || epi == EPI_CLOVINV_ACC;
 }
 
 template <int P, int NE, int EPI>
@@ -667,6 +680,12 @@ inline int launch_epi(const WilsonArgs& A, int nr, int bs, hipStream_t s) {
       case EPI_XMY_RTS: return launch_nr<P, NE, EPI_XMY_RTS>(A, nr, bs, s);
       case EPI_CLOVINV_XPAY: return launch_nr<P, NE, EPI_CLOVINV_XPAY>(A, nr, bs, s);
       case EPI_SITE: return launch_nr<P, NE, EPI_SITE>(A, nr, bs, s);
+      case EPI_RESID:
+        if (A.dag) return -1;
+        return launch_nr<P, NE, EPI_RESID>(A, nr, bs, s);
+      case EPI_CLOVINV_ACC:
+        if (A.dag) return -1;
+        return launch_nr<P, NE, EPI_CLOVINV_ACC>(A, nr, bs, s);
       default: break;
     }
   }
