@@ -87,7 +87,7 @@ __device__ __forceinline__ void hop_fwd(const WilsonArgs& A, const int c[4], int
   const Geom& g = A.g;
   const int pin = par ^ 1;
   cx<R> U[9];
-  const int nb = nb_cb(c, MU, 1, g);
+  const int nb = nb_cb<MU, 1>(c, cb, g);
   load_link<P, NE>(A.links, g.Vh, par, MU, cb, U);
   const bool flip = (MU == 3 && g.ap && c[3] == g.L[3] - 1);
 #pragma unroll
@@ -100,13 +100,8 @@ __device__ __forceinline__ void hop_fwd(const WilsonArgs& A, const int c[4], int
 #pragma unroll
         for (int i = 0; i < 6; ++i) h[i] = -h[i];
       }
-      if constexpr (P == 16) {
-        su3_mv_chain(U, h, uh);
-        su3_mv_chain(U, h + 3, uh + 3);
-      } else {
-        su3_mv(U, h, uh);
-        su3_mv(U, h + 3, uh + 3);
-      }
+      su3_mv(U, h, uh);
+      su3_mv(U, h + 3, uh + 3);
       recon_add<MU, DAG ? 1 : -1>(acc[r], uh);
     }
   }
@@ -119,7 +114,7 @@ __device__ __forceinline__ void hop_bwd(const WilsonArgs& A, const int c[4], int
   const Geom& g = A.g;
   const int pin = par ^ 1;
   cx<R> U[9];
-  const int nb = nb_cb(c, MU, -1, g);
+  const int nb = nb_cb<MU, -1>(c, cb, g);
   load_link<P, NE>(A.links, g.Vh, pin, MU, nb, U);
   const bool flip = (MU == 3 && g.ap && c[3] == 0);
 #pragma unroll
@@ -132,15 +127,191 @@ __device__ __forceinline__ void hop_bwd(const WilsonArgs& A, const int c[4], int
 #pragma unroll
         for (int i = 0; i < 6; ++i) h[i] = -h[i];
       }
-      if constexpr (P == 16) {
-        su3_mv_dag_chain(U, h, uh);
-        su3_mv_dag_chain(U, h + 3, uh + 3);
-      } else {
-        su3_mv_dag(U, h, uh);
-        su3_mv_dag(U, h + 3, uh + 3);
-      }
+      su3_mv_dag(U, h, uh);
+      su3_mv_dag(U, h + 3, uh + 3);
       recon_add<MU, DAG ? -1 : 1>(acc[r], uh);
     }
+  }
+}
+
+// ------------------------------------------------------------ FP16 hops
+// Vector instructions took most of a full-volume launch (3356 per site and two
+// columns, 90% of its time at one per 4 cycles and wave), so the hops read halves
+// where they are used.  v_fma_mix_f32 takes an FP16 operand as an exact FP32 one:
+// the projection is one such instruction per real number, fma(a, 1, +-b) on
+// the halves of two spins, the links are multiplied as halves, and the site's
+// norm (with k_hop and the time-boundary sign) scales the transported vector
+// in the FMA that adds it up.  All sums and products are FP32, and fewer of
+// them round than with every half scaled by its norm first.
+struct Half2 {
+  _Float16 re, im;
+};
+__device__ __forceinline__ float re32(Half2 z) { return (float)z.re; }
+__device__ __forceinline__ float im32(Half2 z) { return (float)z.im; }
+__device__ __forceinline__ float re32(cx<float> z) { return z.re; }
+__device__ __forceinline__ float im32(cx<float> z) { return z.im; }
+__device__ __forceinline__ Half2 half2_of(unsigned w) {
+  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+  const h2 h = __builtin_bit_cast(h2, w);
+  return {h.x, h.y};
+}
+struct Spin16 {
+  Half2 p[12];
+  float n;
+};
+// Column col's spinor at site cb of parity par.  The column's part of the
+// address is a scalar and the parity's a select, so that a lane multiplies for
+// neither (integer multiplications issue at a quarter of the rate).
+__device__ __forceinline__ Spin16 load_spin16(const FieldRef& f, int col, int par, int cb) {
+  const int64_t pv = f.npar == 2 && par ? f.Vh : 0;  // sites before this parity's in the column
+  const uint4* p = (const uint4*)f.data + tix((int64_t)col * f.npar, 0, 3, 0, f.Vh) + (pv * 3 + tix(0, 0, 3, cb, f.Vh));
+  Spin16 s;
+  s.n = f.norm[(int64_t)col * f.npar * f.Vh + (pv + cb)];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const uint4 d = p[tix(0, k, 3, 0, f.Vh)];
+    s.p[4 * k] = half2_of(d.x);
+    s.p[4 * k + 1] = half2_of(d.y);
+    s.p[4 * k + 2] = half2_of(d.z);
+    s.p[4 * k + 3] = half2_of(d.w);
+  }
+  return s;
+}
+// (1 + S g_mu) psi, upper spins; one = 1 behind an asm barrier, so that the sums stay fma_mix
+template <int MU, int S>
+__device__ __forceinline__ void project16(const Half2* p, float one, cx<float>* h) {
+  constexpr float s = (float)S;
+#define LQ_MIX(A, SG, B) __builtin_fmaf((float)(A), one, (SG) * (float)(B))
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const Half2 p0 = p[a], p1 = p[3 + a], p2 = p[6 + a], p3 = p[9 + a];
+    if constexpr (MU == 0) {
+      h[a] = {LQ_MIX(p0.re, s, p3.im), LQ_MIX(p0.im, -s, p3.re)};
+      h[3 + a] = {LQ_MIX(p1.re, s, p2.im), LQ_MIX(p1.im, -s, p2.re)};
+    } else if constexpr (MU == 1) {
+      h[a] = {LQ_MIX(p0.re, -s, p3.re), LQ_MIX(p0.im, -s, p3.im)};
+      h[3 + a] = {LQ_MIX(p1.re, s, p2.re), LQ_MIX(p1.im, s, p2.im)};
+    } else if constexpr (MU == 2) {
+      h[a] = {LQ_MIX(p0.re, s, p2.im), LQ_MIX(p0.im, -s, p2.re)};
+      h[3 + a] = {LQ_MIX(p1.re, -s, p3.im), LQ_MIX(p1.im, s, p3.re)};
+    } else {
+      h[a] = {LQ_MIX(p0.re, s, p2.re), LQ_MIX(p0.im, s, p2.im)};
+      h[3 + a] = {LQ_MIX(p1.re, s, p3.re), LQ_MIX(p1.im, s, p3.im)};
+    }
+  }
+#undef LQ_MIX
+}
+// o += n (1 + S g_mu) h
+template <int MU, int S>
+__device__ __forceinline__ void recon16(cx<float>* o, float n, const cx<float>* h) {
+  const float m = S * n;
+  auto add = [](cx<float>& a, float f, cx<float> z) {  // a += f z
+    a.re = __builtin_fmaf(f, z.re, a.re);
+    a.im = __builtin_fmaf(f, z.im, a.im);
+  };
+  auto add_i = [](cx<float>& a, float f, cx<float> z) {  // a += i f z
+    a.re = __builtin_fmaf(-f, z.im, a.re);
+    a.im = __builtin_fmaf(f, z.re, a.im);
+  };
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const cx<float> h0 = h[a], h1 = h[3 + a];
+    add(o[a], n, h0);
+    add(o[3 + a], n, h1);
+    if constexpr (MU == 0) {
+      add_i(o[6 + a], m, h1);
+      add_i(o[9 + a], m, h0);
+    } else if constexpr (MU == 1) {
+      add(o[6 + a], m, h1);
+      add(o[9 + a], -m, h0);
+    } else if constexpr (MU == 2) {
+      add_i(o[6 + a], m, h0);
+      add_i(o[9 + a], -m, h1);
+    } else {
+      add(o[6 + a], m, h0);
+      add(o[9 + a], m, h1);
+    }
+  }
+}
+// y = U x (ADJ: U^dag x) for the two colour vectors of x
+template <bool ADJ, typename E>
+__device__ __forceinline__ void link16(const E* U, const cx<float>* x, cx<float>* y) {
+#pragma unroll
+  for (int v = 0; v < 2; ++v)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      cx<float> s = {0.f, 0.f};
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        const E u = ADJ ? U[3 * b + a] : U[3 * a + b];
+        const cx<float> z = x[3 * v + b];
+        const float ur = re32(u), ui = ADJ ? -im32(u) : im32(u);
+        s.re = __builtin_fmaf(ur, z.re, s.re);
+        s.re = __builtin_fmaf(-ui, z.im, s.re);
+        s.im = __builtin_fmaf(ur, z.im, s.im);
+        s.im = __builtin_fmaf(ui, z.re, s.im);
+      }
+      y[3 * v + a] = s;
+    }
+}
+// one hop (FWD: x + mu) of NR columns; k = k_hop times what the epilogue scales the sum by
+template <int NE, bool FWD, int S, int MU, int NR>
+__device__ __forceinline__ void hop16(const WilsonArgs& A, const int c[4], int par, int cb, int col0, int nv, float k,
+                                      float one, cx<float> (*acc)[12]) {
+  const Geom& g = A.g;
+  const int pin = par ^ 1, nb = nb_cb<MU, FWD ? 1 : -1>(c, cb, g);
+  const int lpar = FWD ? par : pin, lcb = FWD ? cb : nb;
+  const bool flip = MU == 3 && g.ap && c[3] == (FWD ? g.L[3] - 1 : 0);
+  const float kk = flip ? -k : k;
+  auto columns = [&](const auto* U) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      if (r < nv) {
+        const Spin16 x = load_spin16(A.in, col0 + r, pin, nb);
+        cx<float> h[6], uh[6];
+        project16<MU, S>(x.p, one, h);
+        link16<!FWD>(U, h, uh);
+        recon16<MU, S>(acc[r], kk * x.n, uh);
+      }
+    }
+  };
+  if constexpr (NE == 9) {
+    const unsigned* p = (const unsigned*)A.links + tix(MU, 0, 9, 0, g.Vh) +
+                        ((lpar ? 4 * (int64_t)g.Vh : 0) * 9 + tix(0, 0, 9, lcb, g.Vh));
+    Half2 U[9];
+#pragma unroll
+    for (int e = 0; e < 9; ++e) U[e] = half2_of(p[tix(0, e, 9, 0, g.Vh)]);
+    columns(U);
+  } else {
+    cx<float> U[9];
+    load_link<16, NE>(A.links, g.Vh, lpar, MU, lcb, U);
+    columns(U);
+  }
+}
+// acc = k hop(x), in the hop order of wilson_kernel
+template <int NE, bool DAG, int NR>
+__device__ __forceinline__ void hops16(const WilsonArgs& A, const int c[4], int par, int cb, int col0, int nv, float k,
+                                       cx<float> (*acc)[12]) {
+  constexpr int B = DAG ? -1 : 1;
+  float one = 1.0f;
+  asm volatile("" : "+s"(one));
+  hop16<NE, false, B, 3, NR>(A, c, par, cb, col0, nv, k, one, acc);
+  hop16<NE, false, B, 2, NR>(A, c, par, cb, col0, nv, k, one, acc);
+  hop16<NE, false, B, 1, NR>(A, c, par, cb, col0, nv, k, one, acc);
+  hop16<NE, false, B, 0, NR>(A, c, par, cb, col0, nv, k, one, acc);
+  hop16<NE, true, -B, 0, NR>(A, c, par, cb, col0, nv, k, one, acc);
+  hop16<NE, true, -B, 1, NR>(A, c, par, cb, col0, nv, k, one, acc);
+  hop16<NE, true, -B, 2, NR>(A, c, par, cb, col0, nv, k, one, acc);
+  hop16<NE, true, -B, 3, NR>(A, c, par, cb, col0, nv, k, one, acc);
+}
+// o += f psi of the output site (halves read in the FMA)
+__device__ __forceinline__ void axpy16(const FieldRef& x, int col, int par, int cb, float f, cx<float>* o) {
+  const Spin16 s = load_spin16(x, col, par, cb);
+  const float m = f * s.n;
+#pragma unroll
+  for (int i = 0; i < 12; ++i) {
+    o[i].re = __builtin_fmaf(m, (float)s.p[i].re, o[i].re);
+    o[i].im = __builtin_fmaf(m, (float)s.p[i].im, o[i].im);
   }
 }
 
@@ -258,20 +429,24 @@ wilson_kernel(WilsonArgs A) {
   // closer in time, most for t, whose neighbours are furthest apart, so more
   // of the second reads hit L2 (3% on the 12-column FP32 Schur stencils
   // against forward-backward per direction).
-  hop_bwd<P, NE, DAG, 3, NR>(A, c, par, cb, col0, nv, acc);
-  hop_bwd<P, NE, DAG, 2, NR>(A, c, par, cb, col0, nv, acc);
-  hop_bwd<P, NE, DAG, 1, NR>(A, c, par, cb, col0, nv, acc);
-  hop_bwd<P, NE, DAG, 0, NR>(A, c, par, cb, col0, nv, acc);
-  hop_fwd<P, NE, DAG, 0, NR>(A, c, par, cb, col0, nv, acc);
-  hop_fwd<P, NE, DAG, 1, NR>(A, c, par, cb, col0, nv, acc);
-  hop_fwd<P, NE, DAG, 2, NR>(A, c, par, cb, col0, nv, acc);
-  hop_fwd<P, NE, DAG, 3, NR>(A, c, par, cb, col0, nv, acc);
+  if constexpr (P == 16) {
+    hops16<NE, DAG, NR>(A, c, par, cb, col0, nv, (float)(EPI == EPI_CHEB ? A.s1 * A.k_hop : A.k_hop), acc);
+  } else {
+    hop_bwd<P, NE, DAG, 3, NR>(A, c, par, cb, col0, nv, acc);
+    hop_bwd<P, NE, DAG, 2, NR>(A, c, par, cb, col0, nv, acc);
+    hop_bwd<P, NE, DAG, 1, NR>(A, c, par, cb, col0, nv, acc);
+    hop_bwd<P, NE, DAG, 0, NR>(A, c, par, cb, col0, nv, acc);
+    hop_fwd<P, NE, DAG, 0, NR>(A, c, par, cb, col0, nv, acc);
+    hop_fwd<P, NE, DAG, 1, NR>(A, c, par, cb, col0, nv, acc);
+    hop_fwd<P, NE, DAG, 2, NR>(A, c, par, cb, col0, nv, acc);
+    hop_fwd<P, NE, DAG, 3, NR>(A, c, par, cb, col0, nv, acc);
 
-  const R k = (R)A.k_hop;
+    const R k = (R)A.k_hop;
 #pragma unroll
-  for (int r = 0; r < NR; ++r)
+    for (int r = 0; r < NR; ++r)
 #pragma unroll
-    for (int i = 0; i < 12; ++i) acc[r][i] = k * acc[r][i];
+      for (int i = 0; i < 12; ++i) acc[r][i] = k * acc[r][i];
+  }
 
   if constexpr (EPI == EPI_CLOVINV_XPAY || EPI == EPI_CLOVINV_ACC) {
 #pragma unroll
@@ -319,11 +494,17 @@ wilson_kernel(WilsonArgs A) {
         }
       }
     } else if constexpr (EPI == EPI_XPAY || EPI == EPI_XPAY_NORM || EPI == EPI_XPAY_G5 || EPI == EPI_CHEB) {
-      cx<R> x[12];
-      IO<P, 12>::template load<true>(A.x, blk_index(A.x, col, par), cb, x);
       const R a = A.acol ? (R)A.acol[col] : (R)A.a;
+      if constexpr (P == 16) {
 #pragma unroll
-      for (int i = 0; i < 12; ++i) out[i] = a * x[i] + acc[r][i];
+        for (int i = 0; i < 12; ++i) out[i] = acc[r][i];
+        axpy16(A.x, col, par, cb, EPI == EPI_CHEB ? (float)A.s1 * a : a, out);
+      } else {
+        cx<R> x[12];
+        IO<P, 12>::template load<true>(A.x, blk_index(A.x, col, par), cb, x);
+#pragma unroll
+        for (int i = 0; i < 12; ++i) out[i] = a * x[i] + acc[r][i];
+      }
       if constexpr (EPI == EPI_XPAY_NORM) {
         if (live) {
 #pragma unroll
@@ -335,7 +516,11 @@ wilson_kernel(WilsonArgs A) {
 #pragma unroll
         for (int i = 6; i < 12; ++i) out[i] = -out[i];
       }
-      if constexpr (EPI == EPI_CHEB) {
+      if constexpr (EPI == EPI_CHEB && P == 16) {
+        axpy16(A.v, col, par, cb, (float)A.ck, out);
+        axpy16(A.b1, col, par, cb, (float)A.s2, out);
+        axpy16(A.b2, col, par, cb, -1.0f, out);
+      } else if constexpr (EPI == EPI_CHEB) {
         cx<R> v[12];
         const R s1 = (R)A.s1, ck = (R)A.ck, s2 = (R)A.s2;
         IO<P, 12>::template load<true>(A.v, blk_index(A.v, col, par), cb, v);
@@ -418,7 +603,7 @@ __device__ __forceinline__ void split_hop(const WilsonArgs& A, const int c[4], i
   const Geom& g = A.g;
   const int pin = par ^ 1;
   cx<R> U[9], psi[12], h[6];
-  const int nb = nb_cb(c, MU, S, g);
+  const int nb = nb_cb<MU, S>(c, cb, g);
   load_link<P, NE>(A.links, g.Vh, S > 0 ? par : pin, MU, S > 0 ? cb : nb, U);
   IO<P, 12>::load(A.in, blk_index(A.in, col, pin), nb, psi);
   project<MU, (S > 0) == DAG ? 1 : -1>(psi, h);
