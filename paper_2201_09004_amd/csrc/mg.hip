@@ -356,13 +356,19 @@ __global__ void __launch_bounds__(64) mg_stencil_kernel(MgGeom m, const void* Mv
 // product [Mr | Mi] [[Xr, Xi], [-Xi, Xr]] = [Yr | Yi], done as 16x16x4 MFMA
 // steps (v_mfma_f32_16x16x4f32, or v_mfma_f64_16x16x4f64 for the FP64
 // stencil).  One wave per 16-row tile of M (n2 / 16 waves, the last tile
-// padded), the 24 real output columns in two 16-column tiles (8 padding
-// columns), k in groups of 4; the real and imaginary parts of one loaded
-// matrix element feed the Mr and the Mi step of the same k.  A wave issues all
-// its matrix loads of a direction before its first MFMA.  Lane l holds
+// padded), one 16-column tile for Yr and one for Yi (4 padding columns each; a
+// lane then needs and holds complex numbers, no exchange), k in groups of 4; the
+// real and imaginary parts of one loaded matrix element feed the Mr and the Mi
+// step of the same k.  Lane l holds
 // A[l % 16][l / 16] and B[l / 16][l % 16]; of the output tile it holds
 // D[4 (l / 16) + i][l % 16], i = 0..3, in FP32, and D[4 i + l / 16][l % 16]
-// in FP64.
+// in FP64.  The blocks M are read once and nothing else is comparably large, so
+// their stream is what bounds the kernel: each third of a block is requested two
+// thirds ahead of its products (and before them, since loads complete in order,
+// the wave's share of the next input block).  When every direction waited for
+// its own loads, eight directions of 1728 aggregates, nv = 30, 12 columns (398
+// MB of blocks) took 127 us in FP32 and 155 us in FP64; now 109 us (3.6 TB/s; 43
+// us are matrix products) and 143 us.
 template <int P> struct MfmaT;
 template <> struct MfmaT<32> {
   using R = float;
@@ -379,78 +385,93 @@ template <> struct MfmaT<64> {
   static __device__ __forceinline__ int drow(int q, int i) { return 4 * i + q; }
 };
 
-template <int P>
-__global__ void __launch_bounds__(256) mg_stencil_mfma_kernel(MgGeom m, const void* Mv, int d0, int nd, FieldRef in,
-                                                               FieldRef out, FieldRef x, double a, double sgn,
-                                                               int par_out, int ncol) {
+template <int P, int NKG>  // 4 NKG = n2 rows
+__global__ void __launch_bounds__(64 * ((4 * NKG + 15) / 16))
+mg_stencil_mfma_kernel(MgGeom m, const void* Mv, int d0, int nd, FieldRef in, FieldRef out, FieldRef x, double a,
+                       double sgn, int par_out, int ncol) {
   using T = MfmaT<P>;
   using R = typename T::R;
   using C2 = typename T::C2;
-  __shared__ C2 sx[64 * 12];
-  __shared__ R so[2][64][13];
+  constexpr int n2 = 4 * NKG, NT = 64 * ((n2 + 15) / 16), NE = (12 * n2 + NT - 1) / NT, CH = NKG / 3;
+  static_assert(NKG % 3 == 0, "thirds");
+  __shared__ C2 sx[2][n2 * 12];  // input blocks of this and the next direction
+  __shared__ int sv[9];          // cmap of the neighbours
   const int Y = par_out == 2 ? blockIdx.x : m.csite[par_out * (m.Vc / 2) + blockIdx.x];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r16 = lane & 15, q = lane >> 4;
-  const int n2 = 2 * m.nv, nkg = n2 >> 2;  // n2 <= 60: at most 15 k-groups
   const int col0 = blockIdx.y * 12;
   const int nc = min(12, ncol - col0);
-  const int row = 16 * wv + r16;
-  typename T::V4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
-  for (int d = d0; d < d0 + nd; ++d) {
-    const int Yn = d == 0 ? Y : m.nbr[Y * 8 + d - 1];
-    // this wave's matrix elements of the direction: A[row][4 kg + q], kg < nkg
-    const C2* M = (const C2*)Mv + ((int64_t)Y * 9 + d) * n2 * n2 + row;
-    C2 av[15];
+  if (tid < nd) sv[tid] = m.cmap[d0 + tid == 0 ? Y : m.nbr[Y * 8 + d0 + tid - 1]];
+  // this wave's matrix elements of a direction: A[row][4 kg + q] (rows past the last repeat it, unused)
+  // (a scalar base and one 32-bit offset per lane: the blocks' addresses hold no registers)
+  const char* M0 = (const char*)Mv + ((int64_t)Y * 9 + d0) * (n2 * n2 * (int)sizeof(C2));
+  const unsigned mo = (unsigned)(q * n2 + min(16 * wv + r16, n2 - 1)) * (unsigned)sizeof(C2);
+  auto load_m = [&](int d, int third, C2* av) {
+    const char* M = M0 + (int64_t)d * (n2 * n2 * (int)sizeof(C2));
 #pragma unroll
-    for (int kg = 0; kg < 15; ++kg) {
-      if (kg < nkg && row < n2) av[kg] = M[(int64_t)(4 * kg + q) * n2];
-      else av[kg].x = av[kg].y = 0;
+    for (int k = 0; k < CH; ++k) av[k] = *(const C2*)(M + (third * CH + k) * (4 * n2 * (int)sizeof(C2)) + mo);
+  };
+  // this thread's share of a direction's input block
+  auto load_x = [&](int d, C2* xr) {
+    const int v = sv[d];
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+      const int e = min(tid + i * NT, n2 * 12 - 1), k = e / 12, cc = min(e - k * 12, nc - 1);
+      const int64_t blk = (int64_t)(col0 + cc) * in.npar + (in.npar == 2 ? (v >> 30) & 1 : 0);
+      const auto z = CIO<P>::ld(in, blk, (v & 0x3fffffff) * (n2 / 12) + k / 12, k % 12);
+      xr[i].x = z.re;
+      xr[i].y = z.im;
     }
-    __syncthreads();
-    for (int e = tid; e < n2 * 12; e += blockDim.x) {
-      const int k = e / 12, cc = e - k * 12;
-      const cx<R> v = cc < nc ? cld<P>(in, m, col0 + cc, Yn, k) : cx<R>{0, 0};
-      sx[e].x = v.re;
-      sx[e].y = v.im;
+  };
+  auto store_x = [&](C2* b, const C2* xr) {
+#pragma unroll
+    for (int i = 0; i < NE; ++i)
+      if (tid + i * NT < n2 * 12) b[tid + i * NT] = xr[i];
+  };
+  typename T::V4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+  const int cc16 = min(r16, 11);  // columns past the twelfth repeat it, unused
+  auto multiply = [&](const C2* b, int third, const C2* av) {
+#pragma unroll
+    for (int k = 0; k < CH; ++k) {
+      const C2 xv = b[(4 * (third * CH + k) + q) * 12 + cc16];
+      re = T::mma(av[k].x, xv.x, re);
+      im = T::mma(av[k].x, xv.y, im);
+      re = T::mma(av[k].y, -xv.y, re);
+      im = T::mma(av[k].y, xv.x, im);
     }
-    __syncthreads();
-#pragma unroll
-    for (int kg = 0; kg < 15; ++kg) {
-      if (kg < nkg) {
-        const int k = 4 * kg + q;
-        R bR[2], bI[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const int n = 16 * t + r16;
-          C2 xv;
-          xv.x = xv.y = 0;
-          if (n < 24) xv = sx[k * 12 + (n < 12 ? n : n - 12)];
-          bR[t] = n < 12 ? xv.x : (n < 24 ? xv.y : (R)0);
-          bI[t] = n < 12 ? -xv.y : (n < 24 ? xv.x : (R)0);
-        }
-        acc0 = T::mma(av[kg].x, bR[0], acc0);
-        acc1 = T::mma(av[kg].x, bR[1], acc1);
-        acc0 = T::mma(av[kg].y, bI[0], acc0);
-        acc1 = T::mma(av[kg].y, bI[1], acc1);
-      }
-    }
-  }
-  // D tiles -> [re / im][row][column] in LDS, then one complex output per (row, column)
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int n = 16 * u + r16;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = 16 * wv + T::drow(q, i);
-      const R v = u == 0 ? acc0[i] : acc1[i];
-      if (n < 24 && r < 64) so[n < 12 ? 0 : 1][r][n < 12 ? n : n - 12] = v;
-    }
+  };
+  C2 m0[CH], m1[CH], m2[CH], xr[NE];
+  __syncthreads();
+  if (nd > 0) {
+    load_x(0, xr);
+    load_m(0, 0, m0);
+    load_m(0, 1, m1);
+    store_x(sx[0], xr);
   }
   __syncthreads();
-  for (int e = tid; e < n2 * nc; e += blockDim.x) {
-    const int r = e / nc, cc = e - r * nc;
-    cx<R> o = {(R)sgn * so[0][r][cc], (R)sgn * so[1][r][cc]};
-    if (a != 0.0) o = o + (R)a * cld<P>(x, m, col0 + cc, Y, r);
-    cst<P>(out, m, col0 + cc, Y, r, o);
+  for (int d = 0; d < nd; ++d) {
+    const C2* b = sx[d & 1];
+    const bool more = d + 1 < nd;
+    if (more) load_x(d + 1, xr);
+    load_m(d, 2, m2);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(b, 0, m0);
+    if (more) load_m(d + 1, 0, m0);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(b, 1, m1);
+    if (more) load_m(d + 1, 1, m1);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(b, 2, m2);
+    if (more) store_x(sx[(d + 1) & 1], xr);
+    __syncthreads();
+  }
+  if (r16 >= nc) return;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = 16 * wv + T::drow(q, i);
+    if (r >= n2) continue;
+    cx<R> o = {(R)sgn * re[i], (R)sgn * im[i]};
+    if (a != 0.0) o = o + (R)a * cld<P>(x, m, col0 + r16, Y, r);
+    cst<P>(out, m, col0 + r16, Y, r, o);
   }
 }
 
@@ -970,20 +991,32 @@ int launch_mg_prolong(const MgGeom& m, int pc, FieldRef coarse, int pf, const vo
   return -1;
 }
 
+template <int P, int NKG>
+static int mg_stencil_one(const MgGeom& m, const void* M, int d0, int nd, FieldRef in, FieldRef out, FieldRef x, double a,
+                          double sgn, int par_out, int ncol, hipStream_t s) {
+  dim3 grid(par_out == 2 ? m.Vc : m.Vc / 2, (ncol + 11) / 12);
+  mg_stencil_mfma_kernel<P, NKG><<<grid, 64 * ((4 * NKG + 15) / 16), 0, s>>>(m, M, d0, nd, in, out, x, a, sgn, par_out,
+                                                                            ncol);
+  return hipGetLastError() == hipSuccess ? 0 : -2;
+}
+
 int launch_mg_stencil(const MgGeom& m, int p, const void* M, int d0, int nd, FieldRef in, FieldRef out, FieldRef x,
                       double a, double sgn, int par_out, int ncol, hipStream_t s) {
   if (ncol <= 0) return 0;
   if (2 * m.nv > 64 || d0 < 0 || nd < 0 || d0 + nd > 9 || par_out < 0 || par_out > 2) return -1;
   const bool wide = ncol > 4;
+  // the matrix cores for the widths a hierarchy can have, nv = 6 .. 30 in sixes
+  if (wide && mg_use_mfma()) {
+#define LQ_MG_S(PP, NKG)                                                                                        \
+  if (p == PP && 2 * m.nv == 4 * NKG)                                                                           \
+    return mg_stencil_one<PP, NKG>(m, M, d0, nd, in, out, x, a, sgn, par_out, ncol, s);
+    LQ_MG_S(64, 3) LQ_MG_S(64, 6) LQ_MG_S(64, 9) LQ_MG_S(64, 12) LQ_MG_S(64, 15)
+    LQ_MG_S(32, 3) LQ_MG_S(32, 6) LQ_MG_S(32, 9) LQ_MG_S(32, 12) LQ_MG_S(32, 15)
+#undef LQ_MG_S
+  }
   dim3 grid(par_out == 2 ? m.Vc : m.Vc / 2, wide ? (ncol + 11) / 12 : 1), block(64);
-  if (p == 64 && wide && mg_use_mfma())
-    mg_stencil_mfma_kernel<64><<<grid, dim3(64 * ((2 * m.nv + 15) / 16)), 0, s>>>(m, M, d0, nd, in, out, x, a, sgn,
-                                                                               par_out, ncol);
-  else if (p == 64 && wide) mg_stencil_kernel<64, 12><<<grid, block, 0, s>>>(m, M, d0, nd, in, out, x, a, sgn, par_out, ncol);
+  if (p == 64 && wide) mg_stencil_kernel<64, 12><<<grid, block, 0, s>>>(m, M, d0, nd, in, out, x, a, sgn, par_out, ncol);
   else if (p == 64) mg_stencil_kernel<64, 4><<<grid, block, 0, s>>>(m, M, d0, nd, in, out, x, a, sgn, par_out, ncol);
-  else if (p == 32 && wide && mg_use_mfma())
-    mg_stencil_mfma_kernel<32><<<grid, dim3(64 * ((2 * m.nv + 15) / 16)), 0, s>>>(m, M, d0, nd, in, out, x, a, sgn,
-                                                                               par_out, ncol);
   else if (p == 32 && wide) mg_stencil_kernel<32, 12><<<grid, block, 0, s>>>(m, M, d0, nd, in, out, x, a, sgn, par_out, ncol);
   else if (p == 32) mg_stencil_kernel<32, 4><<<grid, block, 0, s>>>(m, M, d0, nd, in, out, x, a, sgn, par_out, ncol);
   else return -1;
