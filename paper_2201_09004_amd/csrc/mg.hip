@@ -170,6 +170,74 @@ __global__ void __launch_bounds__(256) mg_restrict_kernel(MgGeom m, const void* 
     if (cc < nc) cst<PC>(coarse, m, col0 + cc, Y, t, cx<RC>{(RC)acc[cc].re, (RC)acc[cc].im});
 }
 
+// Restriction of FP32 fine vectors on the matrix cores: for one (aggregate,
+// chirality) the coarse block (nv x 12) is Q^dag (nv x 6 B) times the fine block
+// (6 B rows (site, component) x 12 columns), with v_mfma_f32_16x16x4f32: one or
+// two 16-row tiles of vectors, a 16-column tile each for the real and the
+// imaginary part, k in groups of four sites at one component.  A lane then reads
+// whole site rows: the six components of its vector, and of its column, at its
+// site, 48 bytes each, and nothing is rearranged:
+//   re += qr vr + qi vi,  im += qr vi - qi vr.
+// One wave per (aggregate, chirality); the four waves of a workgroup take
+// consecutive aggregates, which share the cache lines of their fine sites, and
+// consecutive workgroups run on one XCD.  When a thread had a vector, every
+// column's site was read through a load that served two addresses, and the
+// products were formed on the vector units: 1816 us for 12 columns at 24^3x64,
+// nv = 30, 4^4 sites (3.6 GB); now 831 us (910 with an aggregate per workgroup,
+// 857 with those in XCD order).
+template <int PC, int NT>  // NT: 16-row tiles of vectors
+__global__ void __launch_bounds__(256) mg_restrict_mfma_kernel(MgGeom m, const float2* Q, FieldRef fine,
+                                                               FieldRef coarse, int ncol) {
+  const int lb = xcd_remap(blockIdx.x, gridDim.x), s = lb & 1;
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, q = lane >> 4;
+  const int Y = 4 * (lb >> 1) + (tid >> 6);
+  if (Y >= m.Vc) return;
+  const int col0 = blockIdx.y * 12, nc = min(12, ncol - col0);
+  const int nv = m.nv;
+  mg_f4 re[NT], im[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) re[t] = im[t] = {0.f, 0.f, 0.f, 0.f};
+  const int64_t col = col0 + min(r16, nc - 1);  // columns past the last repeat it, unused
+  for (int b0 = 0; b0 < m.B; b0 += 4) {
+    const int b = b0 + q, yb = Y * m.B + min(b, m.B - 1);
+    int cb, par;
+    fine_site(m, yb, cb, par);
+    cx<float> v[6];
+    HalfIO<32>::ld(fine, col * 2 + par, cb, s, v);
+    float4 qv[NT][3];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      // vectors past the last repeat it, unused
+      const float4* p = (const float4*)(Q + (((int64_t)yb * 2 + s) * nv + min(16 * t + r16, nv - 1)) * 6);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) qv[t][c] = p[c];
+    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      // a site past the aggregate's last adds nothing
+      const float vr = b < m.B ? v[c].re : 0.f, vi = b < m.B ? v[c].im : 0.f;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const float4 w = qv[t][c >> 1];
+        const float qr = c & 1 ? w.z : w.x, qi = c & 1 ? w.w : w.y;
+        re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(qr, vr, re[t], 0, 0, 0);
+        im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(qr, vi, im[t], 0, 0, 0);
+        re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(qi, vi, re[t], 0, 0, 0);
+        im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(-qi, vr, im[t], 0, 0, 0);
+      }
+    }
+  }
+  if (r16 >= nc) return;
+  using RC = typename CxT<PC>::R;
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int j = 16 * t + 4 * q + i;
+      if (j < nv) cst<PC>(coarse, m, col0 + r16, Y, s * nv + j, cx<RC>{(RC)re[t][i], (RC)im[t][i]});
+    }
+}
+
 // prolongation: fine(col, y)_s = sum_j coarse(col, Y(y), s nv + j) q_{Y,s,j}(y);
 // one thread per (aggregate site, chirality), CB columns per thread
 template <int PC, int PF, int CB>
@@ -209,93 +277,83 @@ __global__ void __launch_bounds__(256) mg_prolong_kernel(MgGeom m, FieldRef coar
     if (cc < nc) HalfIO<PF>::st(fine, (int64_t)(col0 + cc) * 2 + par, cb, s, acc[cc]);
 }
 
-// Prolongation into FP32 fine vectors on the matrix cores: for one
-// (aggregate, chirality) the fine block F (6 B rows (site, component) x 12
-// columns) is Q (6 B x nv) times the coarse block V (nv x 12), as the real
-// product [Qr | Qi] [[Vr, Vi], [-Vi, Vr]] = [Fr | Fi] with
-// v_mfma_f32_16x16x4f32: 16-row tiles of F, two 16-column tiles for the 24
-// real columns, k (the vector index) in groups of 4 padded to nv rounded up.
-// One workgroup of four waves per (aggregate, chirality), V staged in LDS; each
-// wave takes every fourth row tile and stages its output tile in LDS to write
-// complex pairs.  Lane layouts as in the coarse stencil.
+// Prolongation into FP32 fine vectors on the matrix cores: for one (aggregate,
+// chirality) the fine block (6 B rows (site, component) x 12 columns) is Q (6 B
+// x nv) times the coarse block (nv x 12), with v_mfma_f32_16x16x4f32.  Sixteen
+// sites make six row tiles, one per component, so that a lane reads the six
+// components of its vector at its site, 48 bytes, for all of them; a 16-column
+// tile each holds the real and the imaginary part, and k is the vector index in
+// groups of 4.  A lane ends with all six components of one column at four sites
+// and stores them.  The four waves of a workgroup take consecutive aggregates,
+// which complete each other's cache lines in the fine vector, and a quarter of
+// their groups of 16 sites; the coarse blocks are staged in LDS and a step's rows
+// of Q requested one step ahead.  With row tiles over (site, component) a lane
+// read 8 bytes at a time, and the result went through LDS: 1752 us for 12
+// columns at 24^3x64, nv = 30, 4^4 sites (3.6 GB); now 1385 us (1463 with an
+// aggregate per workgroup), which partly written lines still hold back.
 template <int PC>
 __global__ void __launch_bounds__(256) mg_prolong_mfma_kernel(MgGeom m, FieldRef coarse, const float2* Q,
                                                                FieldRef fine, int ncol) {
-  __shared__ float2 sv[32 * 12];
-  __shared__ float so[4][16][25];
-  const int Y = blockIdx.x >> 1, s = blockIdx.x & 1;
+  __shared__ float2 sv_[4][32 * 12];
+  const int lb = xcd_remap(blockIdx.x, gridDim.x), part = lb & 3, s = (lb >> 2) & 1, Y0 = 4 * (lb >> 3);
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r16 = lane & 15, q = lane >> 4;
   const int col0 = blockIdx.y * 12;
   const int nc = min(12, ncol - col0);
   const int nv = m.nv, nkg = (nv + 3) >> 2;
-  for (int e = tid; e < 32 * 12; e += blockDim.x) {
-    const int j = e / 12, cc = e - j * 12;
+  for (int e = tid; e < 4 * 32 * 12; e += 256) {
+    const int w = e / 384, j = (e - w * 384) / 12, cc = e % 12;
     float2 v = make_float2(0.f, 0.f);
-    if (j < nv && cc < nc) {
-      const auto a = cld<PC>(coarse, m, col0 + cc, Y, s * nv + j);
+    if (j < nv && cc < nc && Y0 + w < m.Vc) {
+      const auto a = cld<PC>(coarse, m, col0 + cc, Y0 + w, s * nv + j);
       v = make_float2((float)a.re, (float)a.im);
     }
-    sv[e] = v;
+    sv_[w][j * 12 + cc] = v;
   }
   __syncthreads();
-  // B operands of this lane for each k-group (the same for every row tile)
-  float bR[8][2], bI[8][2];
+  const int Y = Y0 + wv;
+  if (Y >= m.Vc) return;
+  const float2* sv = sv_[wv];
+  const int cc16 = min(r16, 11);  // columns past the twelfth repeat it, unused
+  for (int b0 = 16 * part; b0 < m.B; b0 += 64) {
+    // sites past the last repeat it, unused
+    const float4* QY = (const float4*)(Q + (((int64_t)Y * m.B + min(b0 + r16, m.B - 1)) * 2 + s) * nv * 6);
+    mg_f4 re[6], im[6];
 #pragma unroll
-  for (int kg = 0; kg < 8; ++kg) {
-    const int k = 4 * kg + q;
+    for (int c = 0; c < 6; ++c) re[c] = im[c] = {0.f, 0.f, 0.f, 0.f};
+    float4 wn[3];
+    auto request = [&](int kg) {  // vectors past the last meet zeros of sv
+      const float4* p = QY + min(4 * kg + q, nv - 1) * 3;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int n = 16 * t + r16;
-      const float2 xv = n < 24 ? sv[k * 12 + (n < 12 ? n : n - 12)] : make_float2(0.f, 0.f);
-      bR[kg][t] = n < 12 ? xv.x : (n < 24 ? xv.y : 0.f);
-      bI[kg][t] = n < 12 ? -xv.y : (n < 24 ? xv.x : 0.f);
-    }
-  }
-  const int rows = 6 * m.B, ntile = (rows + 15) >> 4;
-  const int64_t sstride = (int64_t)2 * nv * 6;  // complex entries between in-block sites
-  const float2* QY = Q + (int64_t)Y * m.B * sstride + (int64_t)s * nv * 6;
-  for (int tile = wv; tile < ntile; tile += 4) {
-    const int row = 16 * tile + r16;
-    const int b = row / 6, c = row - 6 * b;
-    mg_f4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+      for (int c = 0; c < 3; ++c) wn[c] = p[c];
+    };
+    request(0);
+    for (int kg = 0; kg < nkg; ++kg) {
+      const int j = 4 * kg + q;
+      const float4 w[3] = {wn[0], wn[1], wn[2]};
+      request(kg + 1);
+      const float2 x = sv[j * 12 + cc16];
 #pragma unroll
-    for (int kg = 0; kg < 8; ++kg) {
-      if (kg < nkg) {
-        const int j = 4 * kg + q;
-        const float2 av = (row < rows && j < nv) ? QY[(int64_t)b * sstride + j * 6 + c] : make_float2(0.f, 0.f);
-        acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bR[kg][0], acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bR[kg][1], acc1, 0, 0, 0);
-        acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, bI[kg][0], acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, bI[kg][1], acc1, 0, 0, 0);
+      for (int c = 0; c < 6; ++c) {
+        const float qr = c & 1 ? w[c >> 1].z : w[c >> 1].x, qi = c & 1 ? w[c >> 1].w : w[c >> 1].y;
+        re[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(qr, x.x, re[c], 0, 0, 0);
+        im[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(qr, x.y, im[c], 0, 0, 0);
+        re[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(qi, -x.y, re[c], 0, 0, 0);
+        im[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(qi, x.x, im[c], 0, 0, 0);
       }
     }
-    // the wave's output tile through LDS: so[wave][row in tile][real column]
+    if (r16 < nc)
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int n = 16 * u + r16;
+      for (int i = 0; i < 4; ++i) {
+        const int ob = b0 + 4 * q + i;
+        if (ob < m.B) {
+          int cb, par;
+          fine_site(m, Y * m.B + ob, cb, par);
+          cx<float> o[6];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (n < 24) so[wv][4 * q + i][n] = u == 0 ? acc0[i] : acc1[i];
-    }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (int e = lane; e < 16 * 12; e += 64) {
-      const int rr = e / 12, cc = e - rr * 12;
-      const int orow = 16 * tile + rr;
-      if (cc < nc && orow < rows) {
-        const int ob = orow / 6, oc = orow - 6 * ob;
-        int cb, par;
-        fine_site(m, Y * m.B + ob, cb, par);
-        const int comp = 6 * s + oc;
-        float2* p = (float2*)fine.data;
-        p[2 * tix((int64_t)(col0 + cc) * 2 + par, comp >> 1, 6, cb, fine.Vh) + (comp & 1)] =
-            make_float2(so[wv][rr][cc], so[wv][rr][12 + cc]);
+          for (int c = 0; c < 6; ++c) o[c] = {re[c][i], im[c][i]};
+          HalfIO<32>::st(fine, (int64_t)(col0 + r16) * 2 + par, cb, s, o);
+        }
       }
-    }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
 }
 
@@ -948,6 +1006,15 @@ int launch_mg_restrict(const MgGeom& m, int pf, const void* Q, FieldRef fine, in
   if (ncol <= 0) return 0;
   if (2 * m.nv > 64) return -1;
   const bool wide = ncol > 4;
+  if (wide && pf == 32 && mg_use_mfma() && m.nv <= 32) {
+    dim3 g2((m.Vc + 3) / 4 * 2, (ncol + 11) / 12);
+    const float2* q = (const float2*)Q;
+    if (pc == 64 && m.nv > 16) mg_restrict_mfma_kernel<64, 2><<<g2, 256, 0, s>>>(m, q, fine, coarse, ncol);
+    else if (pc == 64) mg_restrict_mfma_kernel<64, 1><<<g2, 256, 0, s>>>(m, q, fine, coarse, ncol);
+    else if (m.nv > 16) mg_restrict_mfma_kernel<32, 2><<<g2, 256, 0, s>>>(m, q, fine, coarse, ncol);
+    else mg_restrict_mfma_kernel<32, 1><<<g2, 256, 0, s>>>(m, q, fine, coarse, ncol);
+    return hipGetLastError() == hipSuccess ? 0 : -2;
+  }
   dim3 grid(m.Vc, wide ? (ncol + 11) / 12 : (ncol + 3) / 4), block(256);
 #define LQ_MG_R(PF, PC)                                                                              \
   if (pf == PF && pc == PC) {                                                                        \
@@ -971,7 +1038,7 @@ int launch_mg_prolong(const MgGeom& m, int pc, FieldRef coarse, int pf, const vo
   // twelve-column version needs all 256 registers
   const bool wide = ncol > 4 && pf == 32;
   if (wide && mg_use_mfma() && m.nv <= 32) {
-    dim3 g2(m.Vc * 2, (ncol + 11) / 12);
+    dim3 g2((m.Vc + 3) / 4 * 8, (ncol + 11) / 12);
     if (pc == 64) mg_prolong_mfma_kernel<64><<<g2, 256, 0, s>>>(m, coarse, (const float2*)Q, fine, ncol);
     else mg_prolong_mfma_kernel<32><<<g2, 256, 0, s>>>(m, coarse, (const float2*)Q, fine, ncol);
     return hipGetLastError() == hipSuccess ? 0 : -2;
