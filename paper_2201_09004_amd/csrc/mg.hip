@@ -283,18 +283,20 @@ __global__ void __launch_bounds__(256) mg_prolong_kernel(MgGeom m, FieldRef coar
 // sites make six row tiles, one per component, so that a lane reads the six
 // components of its vector at its site, 48 bytes, for all of them; a 16-column
 // tile each holds the real and the imaginary part, and k is the vector index in
-// groups of 4.  A lane ends with all six components of one column at four sites
-// and stores them.  The four waves of a workgroup take consecutive aggregates,
-// which complete each other's cache lines in the fine vector, and a quarter of
-// their groups of 16 sites; the coarse blocks are staged in LDS and a step's rows
-// of Q requested one step ahead.  With row tiles over (site, component) a lane
-// read 8 bytes at a time, and the result went through LDS: 1752 us for 12
-// columns at 24^3x64, nv = 30, 4^4 sites (3.6 GB); now 1385 us (1463 with an
-// aggregate per workgroup), which partly written lines still hold back.
+// groups of 4.  The four waves of a workgroup take consecutive aggregates, and a
+// quarter of their groups of 16 sites; the coarse blocks are staged in LDS and a
+// step's rows of Q requested one step ahead.  The results of the four waves meet
+// in LDS, two components at a time, and are written in whole cache lines where
+// the aggregates are neighbours in x and four wide: L2 does not gather parts of
+// lines, each 16 bytes written alone took 2.6 GB of writes for 1.0.  12 columns at
+// 24^3x64, nv = 30, 4^4 sites (3.6 GB): 1752 us when a lane read Q 8 bytes at a
+// time and wrote 8 bytes; 1385 us with these tiles and 16-byte writes; now 927 us
+// (3.9 TB/s).
 template <int PC>
 __global__ void __launch_bounds__(256) mg_prolong_mfma_kernel(MgGeom m, FieldRef coarse, const float2* Q,
                                                                FieldRef fine, int ncol) {
   __shared__ float2 sv_[4][32 * 12];
+  __shared__ float4 so[12 * 65];  // [column][slot], one float4 apart in banks
   const int lb = xcd_remap(blockIdx.x, gridDim.x), part = lb & 3, s = (lb >> 2) & 1, Y0 = 4 * (lb >> 3);
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r16 = lane & 15, q = lane >> 4;
   const int col0 = blockIdx.y * 12;
@@ -310,9 +312,10 @@ __global__ void __launch_bounds__(256) mg_prolong_mfma_kernel(MgGeom m, FieldRef
     sv_[w][j * 12 + cc] = v;
   }
   __syncthreads();
-  const int Y = Y0 + wv;
-  if (Y >= m.Vc) return;
+  const int Y = min(Y0 + wv, m.Vc - 1);
   const float2* sv = sv_[wv];
+  // the site of a group that this thread writes: aggregate ow, in-block b0 + oi
+  const int slot = tid & 63, ow = (slot >> 1) & 3, oi = 4 * (slot >> 4) + 2 * (slot & 1) + ((slot >> 3) & 1);
   const int cc16 = min(r16, 11);  // columns past the twelfth repeat it, unused
   for (int b0 = 16 * part; b0 < m.B; b0 += 64) {
     // sites past the last repeat it, unused
@@ -341,19 +344,24 @@ __global__ void __launch_bounds__(256) mg_prolong_mfma_kernel(MgGeom m, FieldRef
         im[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(qi, x.x, im[c], 0, 0, 0);
       }
     }
-    if (r16 < nc)
+    // two components of the four aggregates' 64 sites at a time through LDS, in an order in which
+    // eight lanes write eight neighbouring sites of one parity (4 wide aggregates)
+    const bool live = Y0 + ow < m.Vc && b0 + oi < m.B;
+    int cb, par;
+    fine_site(m, live ? (Y0 + ow) * m.B + b0 + oi : 0, cb, par);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int ob = b0 + 4 * q + i;
-        if (ob < m.B) {
-          int cb, par;
-          fine_site(m, Y * m.B + ob, cb, par);
-          cx<float> o[6];
+    for (int k = 0; k < 3; ++k) {
+      __syncthreads();
+      if (r16 < 12)
 #pragma unroll
-          for (int c = 0; c < 6; ++c) o[c] = {re[c][i], im[c][i]};
-          HalfIO<32>::st(fine, (int64_t)(col0 + r16) * 2 + par, cb, s, o);
-        }
-      }
+        for (int i = 0; i < 4; ++i)
+          so[r16 * 65 + 16 * q + 8 * (i & 1) + 2 * wv + (i >> 1)] =
+              make_float4(re[2 * k][i], im[2 * k][i], re[2 * k + 1][i], im[2 * k + 1][i]);
+      __syncthreads();
+      if (live)
+        for (int cc = wv; cc < nc; cc += 4)
+          ((float4*)fine.data)[tix((int64_t)(col0 + cc) * 2 + par, 3 * s + k, 6, cb, fine.Vh)] = so[cc * 65 + slot];
+    }
   }
 }
 
