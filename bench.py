@@ -564,8 +564,9 @@ def bench_hisq(args, L, torch):
     value = n_rhs * args.steps / (t1 - t0)
     worst = max(s["true_rel_res"] for s in stats)
     names = [f"stag{p}_{e}" for p in (16, 32, 64) for e in ("hop", "xpay", "xpayd")]
-    vec_names = [f"blas{p}_{o}" for p in (16, 32, 64) for o in BLAS_OPS] + [f"ms{p}_{k}" for p in (16, 32)
-                                                                             for k in ("xr", "p")]
+    vec_names = [f"blas{p}_{o}" for p in (16, 32, 64) for o in BLAS_OPS]
+    vec_names += [f"ms{p}_{k}" for p in (16, 32) for k in ("xr", "p")]
+    vec_names += [f"cg{p}_{k}" for p in (16, 32, 64) for k in ("r", "px")]
     kernels = profile_table(L, ctx, names + [f"{k}_n{n_rhs}" for k in names] + vec_names + ["blas"])
     L.lq_profile(ctx, False)
     # roofline of the kernel family (all launch widths) with the most time in

@@ -331,8 +331,9 @@ lq_status lq_profile_get(lq_ctx *ctx, const char *name, int64_t *count, double *
  * the launches timed under `name` since profiling was enabled.  Names: the
  * stencil kernels as above (wilson32_clovinv, stag16_xpayd, ... and their
  * _n<columns> forms), "blas<prec>_<op>" (axpy, cg, xpay, dot, bicg_xr, ...),
- * "ms<prec>_xr" and "ms<prec>_p" (multi-shift vector kernels) and "blas" for
- * all vector kernels together. */
+ * "cg<prec>_r" and "cg<prec>_px" (the vector kernels of CG), "ms<prec>_xr" and
+ * "ms<prec>_p" (multi-shift vector kernels) and "blas" for all vector kernels
+ * together. */
 lq_status lq_profile_bytes(lq_ctx *ctx, const char *name, double *bytes);
 
 /* Serving: continuous batching of propagator solves (the 12 spin-colour
