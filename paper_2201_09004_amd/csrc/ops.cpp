@@ -378,9 +378,16 @@ static void apply_shape(Args& A, const Shape& sh) {
   A.xcd = sh.xcd;
 }
 
+// whether a kept or loaded shape can be launched: an order of this lattice, and columns per thread of `have`
+static bool shape_usable(const Geom& g, const Shape& sh, const std::vector<int>& have) {
+  return traversal_valid(g, sh.slab) && std::find(have.begin(), have.end(), sh.nr) != have.end() &&
+         (sh.tpb == 0 || sh.tpb == 1 || sh.tpb == 2 || sh.tpb == 4 || sh.tpb == 8);
+}
+
+// nrs: columns per thread worth timing here; have: those the kernel exists for
 template <typename Args, typename LaunchFn>
-static int tuned(lq_ctx* c, const std::string& key, Args& A, size_t out_bytes, int prec,
-                 const std::vector<int>& nrs, hipStream_t s, LaunchFn launch, bool may_tune = true) {
+static int tuned(lq_ctx* c, const std::string& key, Args& A, size_t out_bytes, int prec, const std::vector<int>& nrs,
+                 const std::vector<int>& have, hipStream_t s, LaunchFn launch, bool may_tune = true) {
   Shape choice{1, 0, 0, 1};
   if (const char* f = getenv("LQ_TUNE_FORCE")) {
     // testing hook: force "nr,order[,tpb,xcd]" (nr where it is a candidate, any valid traversal order)
@@ -397,7 +404,7 @@ static int tuned(lq_ctx* c, const std::string& key, Args& A, size_t out_bytes, i
     std::lock_guard<std::mutex> lk(c->mtx);
     tune_load(c);
     auto it = c->tune.find(key);
-    if (it != c->tune.end()) choice = it->second;
+    if (it != c->tune.end() && shape_usable(A.g, it->second, have)) choice = it->second;
     else if (!may_tune) choice = Shape{1, 0, 0, 1};  // untuned default, not recorded
     else if (!tune_enabled()) c->tune[key] = choice;
     else need = true;
@@ -485,6 +492,13 @@ static size_t tune_out_bytes(int prec, int nc, int ncol, int npar, int Vh) {
   return (size_t)ncol * npar * Vh * (size_t)site_bytes(prec, nc);
 }
 
+// the lattice in a tuning key: traversal orders divide its extents, so lattices of one volume share nothing
+static std::string extents(const Geom& g) {
+  char t[64];
+  snprintf(t, sizeof(t), "%dx%dx%dx%d", g.L[0], g.L[1], g.L[2], g.L[3]);
+  return t;
+}
+
 static std::vector<int> nr_candidates(int prec, int ncol, bool blocked, bool split) {
   std::vector<int> v{1};
   if (split) v.push_back(kSplitShape);
@@ -505,7 +519,8 @@ static int run_wilson(OpEnv& e, WilsonArgs& A, int n_fields, int clov_mats, int 
   char name[48];
   snprintf(name, sizeof(name), "wilson%d_%s", A.prec, epi_names[A.epi]);
   char key[160];
-  snprintf(key, sizeof(key), "%s_r%d_d%d_n%d_v%d_p%d", name, A.recon, A.dag, col_bucket(A.ncol), A.g.Vh, A.par_out);
+  snprintf(key, sizeof(key), "%s_r%d_d%d_n%d_l%s_p%d", name, A.recon, A.dag, col_bucket(A.ncol), extents(A.g).c_str(),
+           A.par_out);
   const bool blocked = A.dag ? A.epi == EPI_XPAY || A.epi == EPI_SITE : (A.epi == EPI_CLOVINV || A.epi == EPI_XMY_CLOVINV || A.epi == EPI_XPAY ||
                                   A.epi == EPI_XPAY_G5 || A.epi == EPI_CHEB || A.epi == EPI_XMY_RTS ||
                                   A.epi == EPI_SITE || A.epi == EPI_CLOVINV_XPAY || A.epi == EPI_XPAY_NORM ||
@@ -515,10 +530,10 @@ static int run_wilson(OpEnv& e, WilsonArgs& A, int n_fields, int clov_mats, int 
   // per site against one hop per wave, FP64 twisted-clover D: 64 waves 27 and 19
   // us, 384 waves 33 and 22, 648 waves 36 and 35, 972 waves 38 and 42, 3072
   // waves of one column 107 and 97, of three columns 67 and 88
-  const bool split = A.prec != 16 && (A.dag ? A.epi == EPI_XPAY || A.epi == EPI_SITE
-                                            : A.epi == EPI_HOP || A.epi == EPI_XPAY || A.epi == EPI_XPAY_NORM ||
-                                                  A.epi == EPI_XPAY_G5 || A.epi == EPI_SITE) &&
-                     (int64_t)((nsite + 63) / 64) * A.ncol <= 4096;
+  const bool has_split = A.prec != 16 && (A.dag ? A.epi == EPI_XPAY || A.epi == EPI_SITE
+                                                : A.epi == EPI_HOP || A.epi == EPI_XPAY || A.epi == EPI_XPAY_NORM ||
+                                                      A.epi == EPI_XPAY_G5 || A.epi == EPI_SITE);
+  const bool split = has_split && (int64_t)((nsite + 63) / 64) * A.ncol <= 4096;
   const int out_npar = A.out.npar;
   // timed under the kernel's name and under name_n<columns> (solvers that drop
   // converged columns launch the same kernel at several widths)
@@ -528,7 +543,7 @@ static int run_wilson(OpEnv& e, WilsonArgs& A, int n_fields, int clov_mats, int 
   Prof p(e.noalloc ? nullptr : e.ctx, name, e.s, launch_bytes);
   Prof pn(e.noalloc ? nullptr : e.ctx, name_n, e.s, launch_bytes);
   int r = tuned(e.ctx, key, A, tune_out_bytes(A.prec, 12, A.ncol, out_npar, A.g.Vh), A.prec,
-                nr_candidates(A.prec, A.ncol, blocked, split), e.s,
+                nr_candidates(A.prec, A.ncol, blocked, split), nr_candidates(A.prec, 6, blocked, has_split), e.s,
                 [](const WilsonArgs& B, hipStream_t st) { return launch_wilson(B, st); }, !e.noalloc);
   if (r) return fail(r == -1 ? LQ_ENOTSUP : LQ_EDEVICE, "wilson stencil launch");
   e.n_apply += A.par_out == 2 ? 2 : 1;
@@ -933,10 +948,11 @@ static int run_stag(OpEnv& e, StagArgs& A, int n_fields) {
   char name[48];
   snprintf(name, sizeof(name), "stag%d_%s", A.prec, A.epi == SEPI_HOP ? "hop" : A.epi == SEPI_XPAY ? "xpay" : "xpayd");
   char key[160];
-  snprintf(key, sizeof(key), "%s_n%d_v%d_p%d", name, col_bucket(A.ncol), A.g.Vh, A.par_out);
+  snprintf(key, sizeof(key), "%s_n%d_l%s_p%d", name, col_bucket(A.ncol), extents(A.g).c_str(), A.par_out);
   std::vector<int> nrs{1};
   for (int nr : {2, 3, 4, 6, 8})
     if (nr <= A.ncol && !(A.prec == 64 && nr > 4)) nrs.push_back(nr);
+  const std::vector<int> have{1, 2, 3, 4, 6, 8};
   // timed under the kernel's name and under name_n<columns> (solvers that drop
   // converged columns launch the same kernel at several widths)
   char name_n[64];
@@ -946,7 +962,7 @@ static int run_stag(OpEnv& e, StagArgs& A, int n_fields) {
       (double)nsite * (16 * 18 * rb + (double)A.ncol * n_fields * (6 * rb + (A.prec == 16 ? 4 : 0)));
   Prof p(e.noalloc ? nullptr : e.ctx, name, e.s, launch_bytes);
   Prof pn(e.noalloc ? nullptr : e.ctx, name_n, e.s, launch_bytes);
-  if (tuned(e.ctx, key, A, tune_out_bytes(A.prec, 3, A.ncol, A.out.npar, A.g.Vh), A.prec, nrs, e.s,
+  if (tuned(e.ctx, key, A, tune_out_bytes(A.prec, 3, A.ncol, A.out.npar, A.g.Vh), A.prec, nrs, have, e.s,
             [](const StagArgs& B, hipStream_t st) { return launch_stag(B, st); }, !e.noalloc))
     return fail(LQ_EDEVICE, "staggered stencil launch");
   e.n_apply += A.par_out == 2 ? 2 : 1;
