@@ -223,8 +223,9 @@ lq_status lq_apply_dev(lq_ctx* c, const lq_action* act, const lq_field* g, int o
   if (e) return (lq_status)e;
   if (n_rhs == 0) return LQ_OK;
   hipSetDevice(c->device);
+  WorkCall call(c->device, (hipStream_t)stream);
   e = apply_op(c, act, const_cast<lq_field*>(g), op, prec, n_rhs, in, out, (hipStream_t)stream);
-  if (e) (void)hipStreamSynchronize((hipStream_t)stream);  // its blocks wait for this stream, which the caller may destroy
+  call.idle = e == 0;
   return (lq_status)e;
 }
 
@@ -245,6 +246,7 @@ lq_status lq_apply(lq_ctx* c, const lq_action* act, const lq_field* g, int op, i
   if (n_rhs == 0) return LQ_OK;
   hipSetDevice(c->device);
   const size_t bytes = sizeof(double) * field_doubles(g, act->kind, n_rhs);
+  WorkCall call(c->device, c->stream);
   DBuf din(bytes, c->stream), dout(bytes, c->stream);
   if (!din.p || !dout.p) return (lq_status)fail(LQ_ENOMEM, "staging buffers");
   if (hipMemcpyAsync(din.p, in, bytes, hipMemcpyHostToDevice, c->stream) != hipSuccess)
@@ -254,6 +256,7 @@ lq_status lq_apply(lq_ctx* c, const lq_action* act, const lq_field* g, int op, i
   if (hipMemcpyAsync(out, dout.p, bytes, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
       hipStreamSynchronize(c->stream) != hipSuccess)
     return (lq_status)fail(LQ_EDEVICE, "download");
+  call.idle = true;
   return LQ_OK;
 }
 
@@ -297,8 +300,9 @@ lq_status lq_solve_dev(lq_ctx* c, const lq_action* act, const lq_field* g, const
   if (st) std::memset(st, 0, sizeof(*st));
   if (n_rhs == 0) return LQ_OK;
   hipSetDevice(c->device);
+  WorkCall call(c->device, (hipStream_t)stream);
   e = solve(c, act, const_cast<lq_field*>(g), prm, n_rhs, b, x, st, (hipStream_t)stream);
-  if (e) (void)hipStreamSynchronize((hipStream_t)stream);  // as in lq_apply_dev
+  call.idle = e == 0;
   if (st) st->status = e;
   return (lq_status)e;
 }
@@ -312,6 +316,7 @@ lq_status lq_solve(lq_ctx* c, const lq_action* act, const lq_field* g, const lq_
   hipSetDevice(c->device);
   const size_t nb = sizeof(double) * field_doubles(g, act->kind, n_rhs);
   const size_t nx = sizeof(double) * solution_doubles(g, act, prm, n_rhs);
+  WorkCall call(c->device, c->stream);
   DBuf db(nb, c->stream), dx(nx, c->stream);
   if (!db.p || !dx.p) return (lq_status)fail(LQ_ENOMEM, "staging buffers");
   if (hipMemcpyAsync(db.p, b, nb, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
@@ -324,6 +329,7 @@ lq_status lq_solve(lq_ctx* c, const lq_action* act, const lq_field* g, const lq_
   if (hipMemcpyAsync(x, dx.p, nx, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
       hipStreamSynchronize(c->stream) != hipSuccess)
     return (lq_status)fail(LQ_EDEVICE, "download");
+  call.idle = true;
   g_err = msg;
   return (lq_status)e;
 }
@@ -336,6 +342,7 @@ lq_status lq_eigs(lq_ctx* c, const lq_action* act, const lq_field* g, int which,
   if (act->kind != LQ_OVERLAP) return (lq_status)fail(LQ_EINVAL, "lq_eigs needs the overlap action");
   if (!(act->rho > 0)) return (lq_status)fail(LQ_EINVAL, "lq_eigs: rho must be positive");
   hipSetDevice(c->device);
+  WorkCall call(c->device, c->stream);
   return (lq_status)eigs(c, act, const_cast<lq_field*>(g), which, nev, tol, max_restarts, filter_degree, filter_cut,
                          evals, stats, c->stream);
 }
@@ -345,6 +352,7 @@ lq_status lq_hw_bounds(lq_ctx* c, const lq_action* act, const lq_field* g, int i
   if (g->type != 0) return (lq_status)fail(LQ_EINVAL, "H_W bounds need a Wilson gauge field");
   if (iters < 2) iters = 200;
   hipSetDevice(c->device);
+  WorkCall call(c->device, c->stream);
   int e = hw_bounds(c, act, const_cast<lq_field*>(g), iters, lmin, lmax, c->stream);
   if (!e && hipStreamSynchronize(c->stream) != hipSuccess) e = fail(LQ_EDEVICE, "sync");
   return (lq_status)e;
@@ -355,6 +363,7 @@ lq_status lq_mg_setup(lq_ctx* c, const lq_action* act, const lq_field* g, const 
   int e = check_action(act, g);
   if (e) return (lq_status)e;
   hipSetDevice(c->device);
+  WorkCall call(c->device, c->stream);
   return (lq_status)mg_setup(c, act, const_cast<lq_field*>(g), mp, stats, c->stream);
 }
 
@@ -367,6 +376,7 @@ lq_status lq_mg_apply(lq_ctx* c, const lq_action* act, const lq_field* g, int op
   if (n_rhs > LQ_MAX_COLUMNS) return (lq_status)fail(LQ_EINVAL, "n_rhs above LQ_MAX_COLUMNS");
   if (n_rhs > 0 && (!in || !out)) return (lq_status)fail(LQ_EINVAL, "NULL array");
   hipSetDevice(c->device);
+  WorkCall call(c->device, c->stream);
   return (lq_status)mg_apply_host(c, act, const_cast<lq_field*>(g), op, prec, n_rhs, in, out, c->stream);
 }
 
