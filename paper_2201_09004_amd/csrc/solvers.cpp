@@ -1723,6 +1723,36 @@ int solve(lq_ctx* c, const lq_action* act, lq_field* f, const lq_params* prm, in
 }
 
 // ------------------------------------------------------------------ single application
+// refuses what the action does not define, before the call has touched the stream (which may be under capture)
+static int check_op(int kind, int op) {
+  switch (op) {
+    case LQ_OP_D:
+    case LQ_OP_DDAG:
+    case LQ_OP_HOP: return 0;
+    case LQ_OP_NORMAL_EVEN:
+      if (kind == LQ_HISQ) return 0;
+      break;
+    case LQ_OP_SCHUR:
+      if (kind == LQ_TM_CLOVER) return 0;
+      if (kind != LQ_HISQ) return fail(LQ_EINVAL, "Schur operator needs the twisted-clover action");
+      break;
+    case LQ_OP_SITE:
+    case LQ_OP_SITE_INV:
+      if (kind == LQ_TM_CLOVER) return 0;
+      if (kind != LQ_HISQ) return fail(LQ_EINVAL, "site term needs the twisted-clover action");
+      break;
+    case LQ_OP_HW:
+      if (kind != LQ_HISQ) return 0;
+      break;
+    case LQ_OP_SIGN:
+      if (kind == LQ_OVERLAP) return 0;
+      if (kind != LQ_HISQ) return fail(LQ_EINVAL, "sign function needs the overlap action");
+      break;
+    default: break;
+  }
+  return fail(LQ_EINVAL, kind == LQ_HISQ ? "op not defined for HISQ" : "op not defined for this action");
+}
+
 int apply_op(lq_ctx* c, const lq_action* act, lq_field* f, int op, int prec, int n_rhs, const double* in_dev,
              double* out_dev, hipStream_t s) {
   const Geom& g = f->g;
@@ -1732,12 +1762,12 @@ int apply_op(lq_ctx* c, const lq_action* act, lq_field* f, int op, int prec, int
   const int kind = act->kind;
   const int nc = kind == LQ_HISQ ? 3 : 12;
   if ((kind == LQ_HISQ) != (f->type == 1)) return fail(LQ_EINVAL, "field type does not match the action");
-  int e = 0;
+  int e = check_op(kind, op);
+  if (e) return e;
   // the even-site operators move the even sites alone: one pack, and one unpack
   // that writes the odd sites' zeros with them
   const bool even = kind == LQ_HISQ ? op == LQ_OP_NORMAL_EVEN : op == LQ_OP_SCHUR;
   if (even) {
-    if (kind != LQ_HISQ && kind != LQ_TM_CLOVER) return fail(LQ_EINVAL, "Schur operator needs the twisted-clover action");
     Vec ie = make_vec(g, prec, nc, n_rhs, 1, 0, s), oe = make_vec(g, prec, nc, n_rhs, 1, 0, s),
         to = make_vec(g, prec, nc, n_rhs, 1, 1, s);
     if (!ie.ok() || !oe.ok() || !to.ok()) return fail(LQ_ENOMEM, "apply buffers");
@@ -1755,8 +1785,7 @@ int apply_op(lq_ctx* c, const lq_action* act, lq_field* f, int op, int prec, int
   if (kind == LQ_HISQ) {
     if (op == LQ_OP_D) e = stag_D(env, prec, out, in, false);
     else if (op == LQ_OP_DDAG) e = stag_D(env, prec, out, in, true);
-    else if (op == LQ_OP_HOP) e = stag_hop(env, prec, out, in);
-    else return fail(LQ_EINVAL, "op not defined for HISQ");
+    else e = stag_hop(env, prec, out, in);
   } else {
     if (kind == LQ_OVERLAP && prec == 64 && op != LQ_OP_HW && op != LQ_OP_HOP) {
       if ((e = overlap_prepare(env))) return e;
@@ -1774,16 +1803,14 @@ int apply_op(lq_ctx* c, const lq_action* act, lq_field* f, int op, int prec, int
       case LQ_OP_HOP: e = wilson_hop(env, prec, out, in); break;
       case LQ_OP_SITE:
       case LQ_OP_SITE_INV:
-        if (kind != LQ_TM_CLOVER) return fail(LQ_EINVAL, "site term needs the twisted-clover action");
         e = tm_site(env, prec, out, in, op == LQ_OP_SITE_INV);
         break;
       case LQ_OP_HW: e = hw_apply(env, prec, out, in); break;
       case LQ_OP_SIGN:
-        if (kind != LQ_OVERLAP) return fail(LQ_EINVAL, "sign function needs the overlap action");
         if ((e = overlap_prepare(env))) return e;
         e = sign_apply(env, prec, out, in);
         break;
-      default: return fail(LQ_EINVAL, "op not defined for this action");
+      default: break;  // check_op
     }
   }
   if (e) return e;
