@@ -16,8 +16,7 @@
 // a quarter of the device's memory: beyond that blocks go back to the device
 // (hipFree, which waits for the device's work), as all of them do when an
 // allocation fails and when the last context of the device is finalized.
-// hipStreamPerThread names another stream on every thread: its blocks come
-// from the runtime's pool.
+// hipStreamPerThread names another stream on every thread, as the lists do.
 #include <map>
 #include <mutex>
 #include <thread>
@@ -112,14 +111,6 @@ PinnedPool& pinned() {
 }  // namespace
 
 void* work_alloc(size_t bytes, hipStream_t s) {
-  if (s == hipStreamPerThread) {
-    void* p = nullptr;
-    if (hipMallocAsync(&p, bytes, s) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-    return p;
-  }
   Pools& P = pools();
   const int dev = current_device();
   const size_t n = block_size(bytes);
@@ -146,10 +137,6 @@ void* work_alloc(size_t bytes, hipStream_t s) {
 
 void work_free(void* p, hipStream_t s) {
   if (!p) return;
-  if (s == hipStreamPerThread) {
-    (void)hipFreeAsync(p, s);
-    return;
-  }
   Pools& P = pools();
   std::vector<void*> out;
   {

@@ -1,6 +1,9 @@
 """Working memory of calls on many streams: a stream of its own for every call
 takes no more memory than one stream, also for calls that are refused on the
 way, and the results do not change."""
+import ctypes as C
+import threading
+
 import pytest
 import torch
 
@@ -83,3 +86,37 @@ def test_host_and_device_calls_share_blocks(problem):
         L.lq_apply(ctx, act, f, L.LQ_OP_D, 64, v, want)
         L.lq_apply(ctx, act, f, L.LQ_OP_D, 64, h)
     assert before - free_bytes() <= SLACK
+
+
+def test_per_thread_stream(problem):
+    """hipStreamPerThread (handle 2): its blocks are those of every other stream, and each thread's calls are its own."""
+    ctx, f, v = problem
+    act = L.action(L.LQ_WILSON, m=0.2)
+    want = [L.lq_apply(ctx, act, f, L.LQ_OP_D, p, v) for p in (64, 32)]
+    outs = [torch.empty_like(v) for _ in range(4)]
+
+    def apply_on(stream, prec, out):
+        r = L.load().lq_apply_dev(ctx, C.byref(act), f, L.LQ_OP_D, prec, N, L._ptr(v), L._ptr(out), C.c_void_p(stream))
+        assert r == L.LQ_OK, L.last_error()
+
+    apply_on(2, 64, outs[0])
+    before = free_bytes()
+    apply_on(0, 64, outs[0])
+    apply_on(2, 64, outs[0])
+    assert before - free_bytes() <= SLACK and torch.equal(outs[0], want[0])
+    errors = []
+
+    def thread(k):
+        try:
+            for i in range(6):
+                apply_on(2, (64, 32)[(i + k) % 2], outs[k])
+                assert torch.equal(outs[k], want[(i + k) % 2])
+        except Exception as e:  # reported by the main thread
+            errors.append(e)
+
+    ts = [threading.Thread(target=thread, args=(k,)) for k in range(4)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not errors, errors
