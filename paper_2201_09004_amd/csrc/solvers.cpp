@@ -1540,24 +1540,10 @@ int solve(lq_ctx* c, const lq_action* act, lq_field* f, const lq_params* prm, in
       // solve against 6.5 s for FP16 to 2e-3, 5.7 s for 1e-5, 4.8 s for 1e-6
       // and 1e-7, 4.5 s for 1e-9).
       const int pms = plo == 16 ? LQ_MS_PREC16 : plo;
-      // residuals of the iterations whose x_i and p_i updates are still to be
-      // applied, in turn (FP16 storage applies every iteration by itself, and
-      // fewer are kept where memory is short)
-      std::vector<Vec> ring;
-      const int want = pms == 16 ? 1 : kMsSlots + 1;
-      for (int k = 0; k < want; ++k) {
-        ring.push_back(make_vec(g, pms, 3, n_rhs, 1, 0, s));
-        if (!ring.back().ok()) {
-          ring.pop_back();
-          break;
-        }
-      }
-      // one residual in place, or the newest and those of nslot iterations
-      const int nslot = std::max(1, (int)ring.size() - 1);
-      const bool lazy = ring.size() > 2;
-      if (ring.empty()) return fail(LQ_ENOMEM, "multi-shift buffers");
-      ring.resize(lazy ? nslot + 1 : 1);
+      std::vector<Vec> ring(1);
+      ring.reserve(kMsSlots + 1);
       Vec& r = ring[0];
+      r = make_vec(g, pms, 3, n_rhs, 1, 0, s);
       Vec ap = make_vec(g, pms, 3, n_rhs, 1, 0, s);
       Vec to = make_vec(g, pms, 3, n_rhs, 1, 1, s);
       Vec p = make_vec(g, pms, 3, ncol, 1, 0, s);
@@ -1585,23 +1571,38 @@ int solve(lq_ctx* c, const lq_action* act, lq_field* f, const lq_params* prm, in
       if ((e = blr.op(OP_NORM2, &r))) return e;
       if (launch_ms_init(M, s)) return fail(LQ_EDEVICE, "ms init");
       std::vector<double> hsh((size_t)8 * ncol);
-      // the direction the operator is applied to: column set 0 of p, or with
-      // deferred updates a copy ahead of it
-      Vec pw;
-      if (lazy) {
-        pw = make_vec(g, pms, 3, n_rhs, 1, 0, s);
-        if (!pw.ok()) return fail(LQ_ENOMEM, "multi-shift buffers");
-        if ((e = vec_copy(pw, r))) return e;
-      }
-      Vec p0 = lazy ? view(pw, 0, n_rhs) : view(p, 0, n_rhs);
-      DBuf hist(sizeof(double) * 4 * ncol * nslot, s);
+      DBuf hist(sizeof(double) * 4 * ncol * kMsSlots, s);
       if (!hist.p) return fail(LQ_ENOMEM, "multi-shift scalars");
-      M.pw = p0.f;
-      M.hist = hist.as<double>();
       // <p_0, A p_0> from the stencil epilogue: partials over 64-site tiles
       const int mtiles = (g.Vh + 63) / 64;
       DBuf mred(sizeof(double) * 4 * (size_t)mtiles * n_rhs, s);
       if (!mred.p) return fail(LQ_ENOMEM, "multi-shift partials");
+      // Deferred updates: a ring of residuals, the newest and those of the
+      // iterations whose x_i and p_i updates are still to be applied, and a copy
+      // ahead of p's column set 0, to which the operator is applied.  FP16
+      // storage applies every iteration by itself, with one residual in place,
+      // and so does a device without room for the ring after all that the
+      // iteration needs.
+      Vec pw;
+      bool lazy = pms != 16;
+      if (lazy) {
+        pw = make_vec(g, pms, 3, n_rhs, 1, 0, s);
+        lazy = pw.ok();
+      }
+      while (lazy && (int)ring.size() <= kMsSlots) {
+        ring.push_back(make_vec(g, pms, 3, n_rhs, 1, 0, s));
+        lazy = ring.back().ok();
+      }
+      if (lazy) {
+        if ((e = vec_copy(pw, r))) return e;
+      } else {
+        ring.resize(1);
+        pw = Vec();
+      }
+      const int nslot = lazy ? kMsSlots : 1;
+      Vec p0 = lazy ? view(pw, 0, n_rhs) : view(p, 0, n_rhs);
+      M.pw = p0.f;
+      M.hist = hist.as<double>();
       int it = 0, waiting = 0;  // waiting: iterations whose x_i, p_i updates are deferred
       // x_i and p_i of the waiting iterations
       auto flush = [&]() -> int {
