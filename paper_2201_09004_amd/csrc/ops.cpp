@@ -499,12 +499,12 @@ static std::string extents(const Geom& g) {
   return t;
 }
 
-static std::vector<int> nr_candidates(int prec, int ncol, bool blocked, bool split) {
+static std::vector<int> nr_candidates(int prec, int dag, int ncol, bool blocked, bool split) {
   std::vector<int> v{1};
   if (split) v.push_back(kSplitShape);
   if (!blocked) return v;
   for (int nr : {2, 3, 4, 6})
-    if (nr <= ncol && !(prec == 64 && nr > 4)) v.push_back(nr);
+    if (nr <= ncol && !((prec == 64 || dag) && nr > 4)) v.push_back(nr);
   return v;
 }
 
@@ -543,7 +543,8 @@ static int run_wilson(OpEnv& e, WilsonArgs& A, int n_fields, int clov_mats, int 
   Prof p(e.noalloc ? nullptr : e.ctx, name, e.s, launch_bytes);
   Prof pn(e.noalloc ? nullptr : e.ctx, name_n, e.s, launch_bytes);
   int r = tuned(e.ctx, key, A, tune_out_bytes(A.prec, 12, A.ncol, out_npar, A.g.Vh), A.prec,
-                nr_candidates(A.prec, A.ncol, blocked, split), nr_candidates(A.prec, 6, blocked, has_split), e.s,
+                nr_candidates(A.prec, A.dag, A.ncol, blocked, split),
+                nr_candidates(A.prec, A.dag, 6, blocked, has_split), e.s,
                 [](const WilsonArgs& B, hipStream_t st) { return launch_wilson(B, st); }, !e.noalloc);
   if (r) return fail(r == -1 ? LQ_ENOTSUP : LQ_EDEVICE, "wilson stencil launch");
   e.n_apply += A.par_out == 2 ? 2 : 1;
