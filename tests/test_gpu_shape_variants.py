@@ -35,3 +35,44 @@ def test_daggered_operator(ctx, monkeypatch, kind, prec):
             assert np.array_equal(L.lq_apply(ctx, act, f, L.LQ_OP_DDAG, prec, v), want), shape
     finally:
         L.lq_field_free(f)
+
+
+@pytest.mark.parametrize("sloppy", [64, 32, 16])
+@pytest.mark.parametrize("cols", [5, 7])
+def test_cgne(ctx, monkeypatch, sloppy, cols):
+    """D p with |D p|^2 per column (the fused reduction over ragged column groups): a whole solve."""
+    Lx = (6, 6, 4, 10)
+    f = L.lq_gauge_load(ctx, Lx, synth.su3_field(Lx, 0.3, 73))
+    b = synth.gaussian_spinor(Lx, cols, 74)
+    prm = L.params(tol=1e-9, sloppy_bits=sloppy)
+    act = L.action(L.LQ_WILSON, m=0.2)
+    try:
+        monkeypatch.setenv("LQ_TUNE_FORCE", "1,0")
+        want, st = L.lq_solve(ctx, act, f, prm, b)
+        assert st["status"] == 0
+        for shape in SHAPES:
+            monkeypatch.setenv("LQ_TUNE_FORCE", shape)
+            assert np.array_equal(L.lq_solve(ctx, act, f, prm, b)[0], want), shape
+    finally:
+        L.lq_field_free(f)
+
+
+@pytest.mark.parametrize("cols", [5, 7])
+@pytest.mark.parametrize("nu_pre", [0, 1])
+def test_multigrid_cycle(ctx, monkeypatch, cols, nu_pre):
+    """The cycle's residual, its odd sites added onto the correction, source and Schur stencils."""
+    Lx = (8, 8, 8, 8)
+    f = L.lq_gauge_load(ctx, Lx, synth.su3_field(Lx, 0.2, 81))
+    act = L.action(L.LQ_TM_CLOVER, m=-0.0695, mu=0.01, c_sw=1.0509)
+    b = synth.point_sources(Lx)[:cols]
+    prm = L.params(tol=1e-8, solver=3)
+    try:
+        monkeypatch.setenv("LQ_TUNE_FORCE", "1,0")
+        L.lq_mg_setup(ctx, act, f, L.mg_params(n_vec=6, seed=3, nu_pre=nu_pre, nu_post=2))
+        want, st = L.lq_solve(ctx, act, f, prm, b)
+        assert st["status"] == 0
+        for shape in SHAPES:
+            monkeypatch.setenv("LQ_TUNE_FORCE", shape)
+            assert np.array_equal(L.lq_solve(ctx, act, f, prm, b)[0], want), shape
+    finally:
+        L.lq_field_free(f)
