@@ -222,9 +222,9 @@ int tm_site(OpEnv& e, int prec, Vec& out, const Vec& in, bool inverse);
 // [col][64-site tiles of Vh][4] by the second stencil (EPI_XMY_RTS)
 int tm_schur(OpEnv& e, int prec, Vec& out_e, const Vec& in_e, Vec& tmp_o, int red_mode = 0, double* red = nullptr);
 int tm_schur_source(OpEnv& e, Vec& bhat_e, const Vec& b);                 // in b's precision
-// x full, all in x's precision; add: onto x
+// x full, all in x's precision; add: onto x (FP32)
 int tm_schur_reconstruct(OpEnv& e, Vec& x, const Vec& x_e, const Vec& b, bool add = false);
-int tm_residual(OpEnv& e, int prec, Vec& out, const Vec& b, const Vec& in);  // b - D in (twisted clover)
+int tm_residual(OpEnv& e, Vec& out, const Vec& b, const Vec& in);  // b - D in (twisted clover, FP32)
 // overlap
 int hw_apply(OpEnv& e, int prec, Vec& out, const Vec& in);
 int sign_apply(OpEnv& e, int prec, Vec& out, const Vec& in);

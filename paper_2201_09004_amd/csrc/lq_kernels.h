@@ -80,7 +80,7 @@ int launch_unpack_field(const Geom& g, FieldRef in, int prec, int ncol, int nc, 
                         hipStream_t s, bool zero = false);
 int launch_convert(FieldRef dst, int pdst, FieldRef src, int psrc, int nc, int ncol, int npar, int Vh,
                    hipStream_t s);
-// one parity of dst (npar = 2) = or += src (npar = 1), same precision (64 or 32), Wilson-type
+// one parity of dst (npar = 2) = src (npar = 1), same precision (64 or 32), or += in FP32; Wilson-type
 int launch_parity_put(FieldRef dst, int par, FieldRef src, int prec, int ncol, int Vh, bool add, hipStream_t s);
 double link_maxabs(const double* aos, int64_t n, hipStream_t s);
 

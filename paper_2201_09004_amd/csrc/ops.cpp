@@ -581,7 +581,8 @@ int wilson_D(OpEnv& e, int prec, Vec& out, const Vec& in, bool dag, double* red)
   return run_wilson(e, A, 3, 0, red ? 96 : 48);
 }
 
-int tm_residual(OpEnv& e, int prec, Vec& out, const Vec& b, const Vec& in) {
+int tm_residual(OpEnv& e, Vec& out, const Vec& b, const Vec& in) {
+  const int prec = 32;
   int r = ensure_links(e, prec);
   if (!r) r = ensure_clover(e, prec);
   if (r) return r;

@@ -363,11 +363,10 @@ __global__ void parity_put_kernel(FieldRef dst, int par, FieldRef src, int64_t n
 int launch_parity_put(FieldRef dst, int par, FieldRef src, int prec, int ncol, int Vh, bool add, hipStream_t s) {
   const int64_t n = (int64_t)ncol * Vh;
   if (n == 0) return 0;
-  if (prec == 16 || dst.npar != 2 || src.npar != 1) return -1;
+  if ((prec != 64 && prec != 32) || (add && prec != 32) || dst.npar != 2 || src.npar != 1) return -1;
   const int bs = 256;
   const int nb = (int)((n + bs - 1) / bs);
-  if (prec == 64 && add) parity_put_kernel<64, true><<<nb, bs, 0, s>>>(dst, par, src, n, Vh);
-  else if (prec == 64) parity_put_kernel<64, false><<<nb, bs, 0, s>>>(dst, par, src, n, Vh);
+  if (prec == 64) parity_put_kernel<64, false><<<nb, bs, 0, s>>>(dst, par, src, n, Vh);
   else if (add) parity_put_kernel<32, true><<<nb, bs, 0, s>>>(dst, par, src, n, Vh);
   else parity_put_kernel<32, false><<<nb, bs, 0, s>>>(dst, par, src, n, Vh);
   return hipGetLastError() == hipSuccess ? 0 : -3;

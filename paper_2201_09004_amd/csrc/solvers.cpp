@@ -916,7 +916,7 @@ struct MgCycle {
     // optional pre-smoothing: its correction e_pre, and the coarse level sees r - D e_pre
     Vec* res = &rin;
     if (h.nu_pre > 0) {
-      if ((e = smooth(rin, h.nu_pre, spre, false)) || (e = tm_residual(env, 32, t32, rin, spre))) return e;
+      if ((e = smooth(rin, h.nu_pre, spre, false)) || (e = tm_residual(env, t32, rin, spre))) return e;
       res = &t32;
     }
     // coarse solve on the even aggregates: (1 - A_ee^-1 D_eo A_oo^-1 D_oe) x_e = bhat_e
@@ -934,7 +934,7 @@ struct MgCycle {
     if ((e = mg_prolong(env, h, xc, ev))) return e;
     if (h.nu_pre > 0 && (e = bl.opi(OP_AXPY, &spre, &ev, nullptr, 1.0))) return e;
     // fine-level smoothing on the residual of the correction so far, on the even-odd system
-    if ((e = tm_residual(env, 32, t32, rin, ev)) || (e = smooth(t32, h.nu_post, ev, true))) return e;
+    if ((e = tm_residual(env, t32, rin, ev)) || (e = smooth(t32, h.nu_post, ev, true))) return e;
     ++cycles;
     return z.prec == 32 ? 0 : vec_copy(z, e32);
   }

@@ -318,26 +318,8 @@ __device__ __forceinline__ void axpy16(const FieldRef& x, int col, int par, int 
   }
 }
 
-// 6x6 complex matrix [36] (row-major) times the chiral half of a spinor
-template <int P, typename R>
-__device__ __forceinline__ void apply_full6(const void* base, int Vh, int par, int chir, int cb, const cx<R>* v,
-                                            cx<R>* y) {
-  using T2 = typename LinkT<P>::T2;
-  const T2* p = (const T2*)base;
-  const int g = par * 2 + chir;
-#pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    cx<R> s = {0, 0};
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      T2 d = ldx<true>(p + tix(g, i * 6 + j, 36, cb, Vh));
-      fma(s, cx<R>{(R)d.x, (R)d.y}, v[j]);
-    }
-    y[i] = s;
-  }
-}
-
-// the same for NR columns, each matrix entry loaded once; in place on v[r][off..off+5]
+// 6x6 complex matrix [36] (row-major) times the chiral halves of NR columns, each
+// matrix entry loaded once; in place on v[r][off..off+5]
 template <int P, int NR, typename R>
 __device__ __forceinline__ void apply_full6_nr(const void* base, int Vh, int par, int chir, int cb, int nv,
                                                cx<R> (*v)[12], int off) {
@@ -868,14 +850,13 @@ inline int launch_epi(const WilsonArgs& A, int nr, int bs, hipStream_t s) {
       case EPI_XMY_RTS: return launch_nr<P, NE, EPI_XMY_RTS>(A, nr, bs, s);
       case EPI_CLOVINV_XPAY: return launch_nr<P, NE, EPI_CLOVINV_XPAY>(A, nr, bs, s);
       case EPI_SITE: return launch_nr<P, NE, EPI_SITE>(A, nr, bs, s);
-      case EPI_RESID:
-        if (A.dag) return -1;
-        return launch_nr<P, NE, EPI_RESID>(A, nr, bs, s);
-      case EPI_CLOVINV_ACC:
-        if (A.dag) return -1;
-        return launch_nr<P, NE, EPI_CLOVINV_ACC>(A, nr, bs, s);
       default: break;
     }
+  }
+  if constexpr (P == 32) {  // the multigrid cycle's
+    if (A.dag) return -1;
+    if (A.epi == EPI_RESID) return launch_nr<P, NE, EPI_RESID>(A, nr, bs, s);
+    if (A.epi == EPI_CLOVINV_ACC) return launch_nr<P, NE, EPI_CLOVINV_ACC>(A, nr, bs, s);
   }
   return -1;
 }
