@@ -101,7 +101,7 @@ def profile_table(L, ctx, names):
 
 
 BLAS_OPS = ["axpy", "axmy", "xpay", "cg", "bicg_xr", "bicg_p", "dot", "norm2", "dot_norm", "xmy_norm", "zero",
-            "scale", "g5", "lc_g5", "copy", "plc"]
+            "scale", "g5", "lc_g5", "copy", "gcr_r", "mr0", "mr", "plc"]
 
 
 def family_roofline(kernels, families):
