@@ -380,8 +380,8 @@ __global__ void scalar_gcr_kernel(const double* partial, int gridx, double* st, 
   const double* p = partial + (int64_t)col * gridx * 4;
   const double re = sum_r(p, gridx, 0), im = sum_r(p, gridx, 1), ww = sum_r(p, gridx, 2);
   if (threadIdx.x > 0) return;
+  // a column that is not finite (its source was not) stays so and concerns no other
   const double inv = ww > 0.0 ? 1.0 / ww : 0.0;
-  if (!isfinite(inv) || !isfinite(re) || !isfinite(im)) s[ST_FLAG] = 2;
   s[ST_ALPHA] = alpha[2 * col] = re * inv;
   s[ST_ALPHA + 1] = alpha[2 * col + 1] = im * inv;
   iw2[col] = inv;

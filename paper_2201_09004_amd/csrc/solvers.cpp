@@ -790,10 +790,7 @@ int fgcr_mixed(Blas& bl, const Geom& g, const OpFn& M_hi, const OpFn& M_lo, cons
       if ((e = bl.op(OP_GCR_R, &wk, &rs, nullptr, nullptr, nullptr, st.d(), ST_ALPHA, ST_ALPHA))) return e;
       if (launch_scalar(SC_SET_RR, bl.partial, bl.gridx, n, st.d(), s)) return fail(LQ_EDEVICE, "scalar");
       if ((e = st.pull())) return e;
-      for (int c = 0; c < n; ++c) {
-        if (st.h(c, ST_FLAG) == 2.0) return fail(LQ_ENUMERIC, "GCR: non-finite direction");
-        rr[c] = st.h(c, ST_RR);
-      }
+      for (int c = 0; c < n; ++c) rr[c] = st.h(c, ST_RR);
       ++it;
       ++k;
       if (verbose()) {
