@@ -94,16 +94,33 @@ __device__ __forceinline__ int coords_cb(const int c[4], const Geom& g) {
   return (c[0] >> 1) + g.Lxh * (c[1] + g.L[1] * (c[2] + g.L[2] * c[3]));
 }
 
-// cb index of c + K mu (periodic wrap), K in {-3,-1,1,3}, from the stride of the
-// direction: no multiplications per lane (24 fewer per site in eight hops; FP32
-// staggered hop of 12 columns at 24^3x64 297 -> 293 us, twisted-clover BiCGStab
-// at 16^3x32 3% less).
+// cb index of c + K mu (periodic wrap), K in {-3,-1,1,3}, from the coordinates
+template <int MU, int K>
+__device__ __forceinline__ int nb_coords(const int c[4], const Geom& g) {
+  int d[4] = {c[0], c[1], c[2], c[3]};
+  int v = d[MU] + K;
+  if (v >= g.L[MU]) v -= g.L[MU];
+  if (v < 0) v += g.L[MU];
+  d[MU] = v;
+  return coords_cb(d, g);
+}
+// the same from the stride of the direction: no multiplications per lane (24
+// fewer per site in eight hops; FP32 staggered hop of 12 columns at 24^3x64 297 ->
+// 293 us, twisted-clover BiCGStab at 16^3x32 3% less).  Not for FP64, where three
+// columns per thread then fit two waves per SIMD, which fetch more than one
+// does: H_W of 12 columns at 24^3x64, order fixed, 1797 us by coordinates and
+// 2615 by strides, of 6 columns tuned 806 and 961.
 template <int MU, int K>
 __device__ __forceinline__ int nb_cb(const int c[4], int cb, const Geom& g) {
   const bool wrap = K > 0 ? c[MU] >= g.L[MU] - K : c[MU] < -K;
   const int d = wrap ? K + (K > 0 ? -g.L[MU] : g.L[MU]) : K;
   if constexpr (MU == 0) return cb + ((c[0] + d) >> 1) - (c[0] >> 1);
   else return cb + d * (MU == 1 ? g.Lxh : MU == 2 ? g.Lxh * g.L[1] : g.Lxh * g.L[1] * g.L[2]);
+}
+template <int P, int MU, int K>
+__device__ __forceinline__ int neighbour(const int c[4], int cb, const Geom& g) {
+  if constexpr (P == 64) return nb_coords<MU, K>(c, g);
+  else return nb_cb<MU, K>(c, cb, g);
 }
 
 // ---------------------------------------------------------------- fields

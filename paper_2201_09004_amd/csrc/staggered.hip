@@ -39,8 +39,11 @@ __device__ __forceinline__ void stag_hop1(const StagArgs& A, const int c[4], int
     // Addresses take no multiplications per lane (they issue at a quarter of the
     // rate, and issue bounds the kernel): neighbours by their stride, columns by
     // scalar offsets.  96 columns at 24^3x64: hop 1060 -> 1016 us, with <x, out>
-    // 1300 -> 1251 us; 3 columns at 16^3x32: hop 14.0 -> 12.9 us.
-    const int nb = nb_cb<MU, K>(c, cb, g);
+    // 1300 -> 1251 us.  With three columns per thread the compiler issues fewer
+    // loads ahead when the neighbours come by strides (80 registers, 99 by
+    // coordinates): hop of 3 columns at 24^3x64 119 us with neither, 126 with
+    // both, 114 with neighbours by coordinates.
+    const int nb = NR == 3 ? nb_coords<MU, K>(c, g) : nb_cb<MU, K>(c, cb, g);
     unsigned Ur[9], Ui[9];
     {
       const int lcb = K > 0 ? cb : nb;
@@ -77,7 +80,7 @@ __device__ __forceinline__ void stag_hop1(const StagArgs& A, const int c[4], int
       }
     }
   } else {
-    const int nb = nb_cb<MU, K>(c, cb, g);
+    const int nb = neighbour<P, MU, K>(c, cb, g);
     cx<R> U[9];
     if constexpr (K > 0) load_link<P, 9>(links, g.Vh, par, MU, cb, U);
     else load_link<P, 9>(links, g.Vh, pin, MU, nb, U);

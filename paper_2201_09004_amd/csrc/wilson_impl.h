@@ -87,7 +87,7 @@ __device__ __forceinline__ void hop_fwd(const WilsonArgs& A, const int c[4], int
   const Geom& g = A.g;
   const int pin = par ^ 1;
   cx<R> U[9];
-  const int nb = nb_cb<MU, 1>(c, cb, g);
+  const int nb = neighbour<P, MU, 1>(c, cb, g);
   load_link<P, NE>(A.links, g.Vh, par, MU, cb, U);
   const bool flip = (MU == 3 && g.ap && c[3] == g.L[3] - 1);
 #pragma unroll
@@ -114,7 +114,7 @@ __device__ __forceinline__ void hop_bwd(const WilsonArgs& A, const int c[4], int
   const Geom& g = A.g;
   const int pin = par ^ 1;
   cx<R> U[9];
-  const int nb = nb_cb<MU, -1>(c, cb, g);
+  const int nb = neighbour<P, MU, -1>(c, cb, g);
   load_link<P, NE>(A.links, g.Vh, pin, MU, nb, U);
   const bool flip = (MU == 3 && g.ap && c[3] == 0);
 #pragma unroll
