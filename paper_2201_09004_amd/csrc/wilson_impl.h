@@ -142,10 +142,12 @@ __device__ __forceinline__ void hop_bwd(const WilsonArgs& A, const int c[4], int
 // the halves of two spins, the links are multiplied as halves, and the site's
 // norm (with k_hop and the time-boundary sign) scales the transported vector
 // in the FMA that adds it up.  All sums and products are FP32, and fewer of
-// them round than with every half scaled by its norm first.  That leaves 2585,
-// and what bounds the launch now are its 2.5 GB (3.9 with the Chebyshev
-// operands) at 5.1 - 5.4 TB/s.  12 columns at 24^3x64: g5 (a x + k hop) 592 -> 486
-// us, the Clenshaw step 773 -> 722 us.
+// them round than with every half scaled by its norm first (the sign function of
+// order 200 is as far from FP64 as before, 8.175e-4 at 24^3x64, its FP16 state
+// being what rounds).  That leaves 2585, and traffic bounds the launch now: 2.5 GB
+// across the L2 boundary for 1.36 GB of operands (the Clenshaw step 4.0 for 2.46)
+// at 5.1 - 5.5 TB/s.  12 columns at 24^3x64: g5 (a x + k hop) 592 -> 486 us, the
+// Clenshaw step 773 -> 722 us.
 struct Half2 {
   _Float16 re, im;
 };
