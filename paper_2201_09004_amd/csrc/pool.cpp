@@ -12,14 +12,15 @@
 // its stream, the blocks of its list move to one that serves every stream, so
 // that a caller's streams may come and go (with a list kept per stream, twenty
 // Schur applications at 24^3x64 on streams of their own held 27 GiB; on one, 1.4
-// GiB).  So do the blocks of a stream that the library destroys.  What waits is bounded by
-// a quarter of the device's memory: beyond that blocks go back to the device
-// (hipFree, which waits for the device's work), as all of them do when an
-// allocation fails and when the last context of the device is finalized; the
-// pinned blocks go with the last context of all.  HISQ with 12 columns and 8
-// masses at 32^3x96, all sites, which reaches the bound in every call: 3.94 s,
-// with three quarters as the bound 3.91 s.
+// GiB).  So do the blocks of a stream that the library destroys.
 // hipStreamPerThread names another stream on every thread, as the lists do.
+//
+// What waits is bounded by a quarter of the device's memory: beyond that blocks
+// go back to the device (hipFree, which waits for the device's work), as all of
+// them do when an allocation fails and when the last context of the device is
+// finalized; the pinned blocks go with the last context of all.  HISQ with 12
+// columns and 8 masses at 32^3x96, all sites, which reaches the bound in every
+// call: 3.94 s, with three quarters as the bound 3.91 s.
 #include <map>
 #include <mutex>
 #include <thread>
@@ -185,7 +186,10 @@ WorkCall::~WorkCall() {
     auto it = d.by_owner.find(me(s));
     if (it == d.by_owner.end()) return;
   }
-  if (!idle && hipStreamSynchronize(s) != hipSuccess) return;
+  if (!idle && hipStreamSynchronize(s) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
   std::lock_guard<std::mutex> lk(P.m);
   auto it = d.by_owner.find(me(s));
   if (it == d.by_owner.end()) return;
